@@ -993,6 +993,8 @@ void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
     auto* sten_d = reinterpret_cast<int32_t*>(base + a.sten_d);
     auto* Bd = reinterpret_cast<T*>(base + a.Bd);
     auto* O = reinterpret_cast<T*>(base + a.O);
+    auto* th = reinterpret_cast<T*>(base + a.th);
+    auto* mom = reinterpret_cast<T*>(base + a.mom);
     auto* xi = reinterpret_cast<T*>(base + a.xi);
     auto* pmean = reinterpret_cast<T*>(base + a.pmean);
     auto* c2f = reinterpret_cast<int32_t*>(base + a.c2f);
@@ -1062,8 +1064,18 @@ void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
             }
         }
         int t = 0;
-        for (int k = 0; k < K; ++k)
-            for (int l = k; l < K; ++l) O[size_t(t++) * nc + c] = T(m.O[(size_t(c) * K + k) * K + l]);
+        if (m.order == 4)
+            for (int k = 0; k < K; ++k)
+                for (int l = k; l < K; ++l) O[size_t(t++) * nc + c] = T(m.O[(size_t(c) * K + k) * K + l]);
+        const double h = m.hb[c];
+        th[c] = T(std::pow(m.vol[c], 2.0 / 3.0) / (h * h));
+        if (m.order == 3) {
+            int r = 0;
+            for (int i = 4; i >= 0; --i)
+                for (int j = 4 - i; j >= 0; --j)
+                    mom[size_t(r++) * nc + c] = T(m.moments[size_t(c) * m.nmom + mom_index(m.mom_deg, i, j, 4 - i - j)] /
+                                                  (m.vol[c] * std::pow(h, 4)));
+        }
         for (int k = 0; k < K; ++k) pmean[size_t(k) * nc + c] = T(m.mean[size_t(c) * K + k]);
         for (int lf = 0; lf < NF; ++lf) {
             const int32_t fs = m.c2f[c * kMaxFaces + lf];
@@ -1107,7 +1119,9 @@ int pack_arena(const Mesh& m, int precision, Arena& a, std::vector<unsigned char
     a.ndir = take(nc);
     a.sten_d = take(4 * ND * MD * nc);
     a.Bd = take(ts * ND * m.kd * MD * nc);
-    a.O = take(ts * K * (K + 1) / 2 * nc);
+    a.O = take(m.order == 4 ? ts * K * (K + 1) / 2 * nc : 0);
+    a.th = take(ts * nc);
+    a.mom = take(ts * num_indicator_moments(m.order) * nc);
     a.xi = take(ts * NF * Q * 3 * nc);
     a.pmean = take(ts * K * nc);
     a.c2f = take(4 * NF * nc);

@@ -303,30 +303,117 @@ __device__ __forceinline__ void gate_features(const ReconArgs<T>& A, int64_t c, 
 //  (vii) point values U_i + Phi_q . abar at the cell's face points, with the
 //        positivity fallback linear -> CWENOZ -> first order.
 
-// SI_1 = a^T O a with O stored as its upper triangle; a sum of squares, so a
-// rounded value below zero is rounding only and is clamped.
+// Exponents of the monomials of degree 1..4 in graded-lex order (the basis
+// order; the first K of them at P2/P3, all 34 with degree 4), and the inverse.
+struct MonoTable {
+    int e[34][3] = {};
+    int at[5][5][5] = {};
+    constexpr MonoTable() {
+        int k = 0;
+        for (int d = 1; d <= 4; ++d)
+            for (int i = d; i >= 0; --i)
+                for (int j = d - i; j >= 0; --j) {
+                    e[k][0] = i;
+                    e[k][1] = j;
+                    e[k][2] = d - i - j;
+                    at[i][j][d - i - j] = k++;
+                }
+    }
+};
+constexpr MonoTable kMono{};
+constexpr int mono_at(int i, int j, int k) { return i + j + k == 0 ? -1 : kMono.at[i][j][k]; }
+
+// SI_1 per variable: the quadratic form a^T O a of the indicator matrix
+// O_kl = sum_{1<=|b|<=r} V^(2|b|/3 - 1) int D^b phi_k D^b phi_l, evaluated as
+// what it is, sum_b theta^|b| mean((D^b p)^2) with theta = V^(2/3)/h^2 and
+// derivatives in the scaled frame.  The means are quadratic forms of p's
+// derivative coefficients with the cell's scaled moments (the basis means,
+// which are the moments up to degree r, and at P3 the 15 of degree 4; the
+// first moments about the centroid vanish), so a cell reads 7 (P2) or 32
+// (P3) values instead of O's 45 or 190 entries, at about as many
+// multiply-adds.  The calls are bound by HBM, so the bytes are what counts:
+// FP64 64^3 hex P2 call 332 -> 312 us, 196,608 P3 tets 443 -> 404 us, gated
+// FP32 shocked tets 215 -> 204 us.
 template <class T, int K>
 __device__ __forceinline__ void si_opt(const ReconArgs<T>& A, int64_t c, const T a[K][5], T SI1[5]) {
+    static_assert(K == 9 || K == 19);
+    constexpr int R = K == 9 ? 2 : 3;         // degree
+    constexpr int ND = R == 2 ? 4 : 10;       // coefficients of a first derivative (degree R - 1)
+    constexpr int NM = R == 2 ? 9 : 34;       // moments of degree 1 .. 2 R - 2
     const int64_t nc = A.nc;
+    const T th = A.th[c];
+    T M[NM];
+    static_for<3, K>([&](auto k) { M[k] = A.pmean[int64_t(k) * nc + c]; });
+    if constexpr (R == 3) static_for<K, NM>([&](auto k) { M[k] = A.mom[int64_t(k - K) * nc + c]; });
+    // entry (i, j) of the moment matrix of (1, monomials); -1 stands for 1
+    auto mean = [&](auto I, auto J) -> T {
+        constexpr int i = decltype(I)::value - 1, j = decltype(J)::value - 1;
+        constexpr int x = (i < 0 ? 0 : kMono.e[i < 0 ? 0 : i][0]) + (j < 0 ? 0 : kMono.e[j < 0 ? 0 : j][0]);
+        constexpr int y = (i < 0 ? 0 : kMono.e[i < 0 ? 0 : i][1]) + (j < 0 ? 0 : kMono.e[j < 0 ? 0 : j][1]);
+        constexpr int z = (i < 0 ? 0 : kMono.e[i < 0 ? 0 : i][2]) + (j < 0 ? 0 : kMono.e[j < 0 ? 0 : j][2]);
+        constexpr int m = mono_at(x, y, z);
+        if constexpr (m < 0)
+            return T(1);
+        else
+            return M[m < 0 ? 0 : m];
+    };
+    // mean((sum_i q_i mono_i)^2) over i = 0 (the constant) .. N - 1
+    auto form = [&](auto NN, const T* q) {
+        constexpr int N = decltype(NN)::value;
+        T s = T(0);
+        static_for<0, N>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            T t = T(0);
+            static_for<i + 1, N>([&](auto J) {
+                constexpr int j = decltype(J)::value;
+                if constexpr (i > 0 || j > 3) t += mean(I, J) * q[j];  // first moments vanish
+            });
+            s += q[i] * (mean(I, I) * q[i] + T(2) * t);
+        });
+        return s;
+    };
 #pragma unroll
-    for (int v = 0; v < 5; ++v) SI1[v] = T(0);
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const T okk = A.O[int64_t(tri_index(K, k, k)) * nc + c];
-        T t[5];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) t[v] = okk * a[k][v];
-#pragma unroll
-        for (int l = k + 1; l < K; ++l) {
-            const T o2 = T(2) * A.O[int64_t(tri_index(K, k, l)) * nc + c];
-#pragma unroll
-            for (int v = 0; v < 5; ++v) t[v] += o2 * a[l][v];
-        }
-#pragma unroll
-        for (int v = 0; v < 5; ++v) SI1[v] += a[k][v] * t[v];
+    for (int v = 0; v < 5; ++v) {
+        T S[3] = {T(0), T(0), T(0)};  // by order of the derivative
+        static_for<0, 3>([&](auto D) {
+            constexpr int d = decltype(D)::value;
+            T q[ND];
+            static_for<0, ND>([&](auto I) {
+                constexpr int i = decltype(I)::value - 1;
+                constexpr int e0 = i < 0 ? 0 : kMono.e[i < 0 ? 0 : i][0], e1 = i < 0 ? 0 : kMono.e[i < 0 ? 0 : i][1],
+                              e2 = i < 0 ? 0 : kMono.e[i < 0 ? 0 : i][2];
+                constexpr int k = mono_at(e0 + (d == 0), e1 + (d == 1), e2 + (d == 2));
+                constexpr int f = (d == 0 ? e0 : d == 1 ? e1 : e2) + 1;
+                q[I] = T(f) * a[k][v];
+            });
+            S[0] += form(std::integral_constant<int, ND>{}, q);
+        });
+        // second derivatives: constants at P2, linear polynomials at P3
+        static_for<3, 9>([&](auto B) {
+            constexpr int b = decltype(B)::value, N = R == 2 ? 1 : 4;
+            T q[N];
+            static_for<0, N>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                constexpr int e0 = kMono.e[b][0] + (i == 1), e1 = kMono.e[b][1] + (i == 2), e2 = kMono.e[b][2] + (i == 3);
+                constexpr int k = mono_at(e0, e1, e2);
+                // D^b x^e = (e)_b x^(e - b) with falling factorials (degrees at most 3)
+                constexpr auto fall = [](int e, int n) { return n == 0 ? 1 : n == 1 ? e : n == 2 ? e * (e - 1) : e * (e - 1) * (e - 2); };
+                constexpr int f = fall(e0, kMono.e[b][0]) * fall(e1, kMono.e[b][1]) * fall(e2, kMono.e[b][2]);
+                q[I] = T(f) * a[k][v];
+            });
+            S[1] += form(std::integral_constant<int, N>{}, q);
+        });
+        if constexpr (R == 3)
+            static_for<9, 19>([&](auto B) {  // third derivatives: constants
+                constexpr int b = decltype(B)::value;
+                constexpr auto fact = [](int n) { return n == 3 ? 6 : n == 2 ? 2 : 1; };
+                constexpr int f = fact(kMono.e[b][0]) * fact(kMono.e[b][1]) * fact(kMono.e[b][2]);
+                const T q = T(f) * a[b][v];
+                S[2] += q * q;
+            });
+        SI1[v] = th * (S[0] + th * (S[1] + th * S[2]));
+        SI1[v] = fmax(SI1[v], T(0));
     }
-#pragma unroll
-    for (int v = 0; v < 5; ++v) SI1[v] = fmax(SI1[v], T(0));
 }
 
 // Basis functions at a face point from its offset (x, y, z) in the cell's
@@ -481,12 +568,11 @@ template <class T>
 struct Blend {
     T lam_s, lam_1;
     T SI1[5], inv1[5], tsum[5], Lam[5], rmin[5], rmax[5], g[3][5];
-    T o00, o01, o02, o11, o12, o22;  // the linear block of O
+    T th;  // the linear block of O is th times the identity
 };
 
 template <class T, int K>
 __device__ __forceinline__ void blend_init(const ReconArgs<T>& A, int64_t c, int nd, const T a[K][5], Blend<T>& B) {
-    const int64_t nc = A.nc;
     B.lam_s = T(1) / (A.lam_c + T(nd));
     B.lam_1 = A.lam_c * B.lam_s;
     si_opt<T, K>(A, c, a, B.SI1);
@@ -500,12 +586,7 @@ __device__ __forceinline__ void blend_init(const ReconArgs<T>& A, int64_t c, int
 #pragma unroll
         for (int k = 0; k < 3; ++k) B.g[k][v] = T(0);
     }
-    B.o00 = A.O[0 * nc + c];
-    B.o01 = A.O[1 * nc + c];
-    B.o02 = A.O[2 * nc + c];
-    B.o11 = A.O[int64_t(K) * nc + c];
-    B.o12 = A.O[int64_t(K + 1) * nc + c];
-    B.o22 = A.O[int64_t(2 * K - 1) * nc + c];
+    B.th = A.th[c];
 }
 
 // One directional stencil with linear coefficients as: its indicator and its
@@ -515,9 +596,7 @@ __device__ __forceinline__ void blend_add(const ReconArgs<T>& A, Blend<T>& B, co
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
         const T x = as[0][v], y = as[1][v], z = as[2][v];
-        const T SIs = fmax(x * (B.o00 * x + T(2) * (B.o01 * y + B.o02 * z)) + y * (B.o11 * y + T(2) * B.o12 * z) +
-                               z * B.o22 * z,
-                           T(0));
+        const T SIs = fmax(B.th * (x * x + y * y + z * z), T(0));
         B.tsum[v] += fabs(B.SI1[v] - SIs);
         const T r = T(1) / (A.eps + SIs);
         B.Lam[v] += B.lam_s * r;
@@ -922,16 +1001,12 @@ __device__ __forceinline__ void dir_blend_stencils(const ReconArgs<float>& A, ui
             for (int k = 0; k < 3; ++k) gg[k][v] = T(0);
         }
         if (work) {
-            const T o00 = A.O[0 * nc + cq], o01 = A.O[1 * nc + cq], o02 = A.O[2 * nc + cq];
-            const T o11 = A.O[int64_t(K) * nc + cq], o12 = A.O[int64_t(K + 1) * nc + cq];
-            const T o22 = A.O[int64_t(2 * K - 1) * nc + cq];
+            const T th = A.th[cq];
             const T lam_s = T(1) / (A.lam_c + T(ndp));
 #pragma unroll
             for (int v = 0; v < 5; ++v) {
                 const T x = as[0][v], y = as[1][v], z = as[2][v];
-                const T SIs = fmax(x * (o00 * x + T(2) * (o01 * y + o02 * z)) + y * (o11 * y + T(2) * o12 * z) +
-                                       z * o22 * z,
-                                   T(0));
+                const T SIs = fmax(th * (x * x + y * y + z * z), T(0));
                 ts[v] = fabs(SI1p[v] - SIs);
                 const T r = T(1) / (A.eps + SIs);
                 lm[v] = lam_s * r;

@@ -53,6 +53,9 @@ constexpr uint64_t kMaxDescriptorBytes = 0xffffffffull;
 struct Arena {
     size_t bytes = 0;
     size_t sten_c = 0, Bc = 0, ndir = 0, sten_d = 0, Bd = 0, O = 0, xi = 0, pmean = 0, c2f = 0;
+    // smoothness indicators: V^(2/3) / h^2 per cell, and the scaled moments of degree r+1 .. 2r-2
+    // (pmean holds those up to r), which fix the indicator matrix; P4 still reads the matrix O
+    size_t th = 0, mom = 0;
     size_t cnq = 0;  // [nfmax][nc] Gauss points of each of a cell's face slots (0: no face)
     size_t vol = 0, hdt = 0, fcell = 0, flf = 0, fnrm = 0, farea = 0, fw = 0, fdc = 0, fnq = 0;
     // face neighbours ([nfmax][nc]; a boundary slot holds its face's negative tag, an absent one -1),
@@ -63,6 +66,11 @@ struct Arena {
     size_t ustage = 0;  // P4 only: [nc][8] FP64, the state staged cell-interleaved by each reconstruction call
     void* dev = nullptr;  // caller-owned device pointer after upload
 };
+
+// Scaled moments mean(((x - c)/h)^e) of degree r+1 .. 2r-2 (P2: none, P3: the
+// 15 of degree 4), the ones the smoothness indicators need beside the basis
+// means; in the basis' graded-lex order, degree by degree.
+constexpr int num_indicator_moments(int order) { return order == 3 ? 15 : 0; }
 
 struct Mesh {
     // ---- input

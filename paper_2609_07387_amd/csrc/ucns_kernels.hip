@@ -95,7 +95,9 @@ struct ReconArgs {
     const T* Bd;
     int ND;       // directional stencil slots per cell (cells with fewer pad with zero operators)
     int MD;       // padded directional stencil size
-    const T* O;
+    const T* O;    // P4: upper triangle of the indicator matrix
+    const T* th;   // V^(2/3) / h^2 per cell
+    const T* mom;  // P3: scaled moments of degree 4 [15][nc]
     const T* xi;     // face points in each cell's scaled frame [lf][q][3][nc]
     const T* pmean;  // cell means of the scaled monomials [K][nc]
     const uint8_t* cnq;  // Gauss points of each face slot [lf][nc] (0: no face)
@@ -997,6 +999,8 @@ ReconArgs<T> make_recon_args(const Mesh& m, const Arena& ar, double gm1, const d
     A.ND = std::max(1, m.nd_max);
     A.MD = std::max(1, m.md_pad);
     A.O = arena_ptr<T>(ar, ar.O);
+    A.th = arena_ptr<T>(ar, ar.th);
+    A.mom = arena_ptr<T>(ar, ar.mom);
     A.xi = arena_ptr<T>(ar, ar.xi);
     A.pmean = arena_ptr<T>(ar, ar.pmean);
     A.cnq = arena_ptr<uint8_t>(ar, ar.cnq);
