@@ -900,6 +900,7 @@ int build_mesh(const ucns_mesh_desc* d, const ucns_recon_opts* o, int n_threads,
     for (int a = 0; a < 3; ++a) m->period[a] = d->period[a];
     m->order = o->order;
     m->K = (o->order + 1) * (o->order + 2) * (o->order + 3) / 6 - 1;
+    m->ns = row_stride(m->nc, m->K);
     // directional polynomials: linear for the third- and fourth-order
     // schemes, quadratic for the fifth (Sec. 2.2)
     m->kd = o->order >= 4 ? 9 : 3;
@@ -984,7 +985,7 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 template <class T>
 void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
-    const int64_t nc = m.nc, nf = m.nf;
+    const int64_t nc = m.nc, nf = m.nf, ns = m.ns;
     const int K = m.K, Q = m.qmax, NF = m.nfmax, MC = m.mc_pad, ND = std::max(1, m.nd_max), MD = std::max(1, m.md_pad);
     const int KD = m.kd;
     auto* sten_c = reinterpret_cast<int32_t*>(base + a.sten_c);
@@ -1017,7 +1018,7 @@ void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
     for (int64_t c = 0; c < nc; ++c) {
         hb[c] = T(m.hb[c]);
         for (int lf = 0; lf < NF; ++lf)
-            for (int k = 0; k < 3; ++k) glsq[(size_t(lf) * 3 + k) * nc + c] = T(m.glsq[(size_t(c) * kMaxFaces + lf) * 3 + k]);
+            for (int k = 0; k < 3; ++k) glsq[(size_t(lf) * 3 + k) * ns + c] = T(m.glsq[(size_t(c) * kMaxFaces + lf) * 3 + k]);
         ncen[c] = uint8_t(m.ncen[c]);
         for (int lf = 0; lf < NF; ++lf) {
             const int32_t fs = m.c2f[c * kMaxFaces + lf];
@@ -1032,10 +1033,10 @@ void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
                 const double s = (side ? -0.5 : 0.5) * m.farea[f] / m.vol[c];
                 for (int k = 0; k < 3; ++k) w[k] = s * m.fnrm[3 * f + k];
             }
-            nbr[size_t(lf) * nc + c] = j;
+            nbr[size_t(lf) * ns + c] = j;
             for (int k = 0; k < 3; ++k) {
-                ndc[(size_t(lf) * 3 + k) * nc + c] = T(d[k]);
-                ggw[(size_t(lf) * 3 + k) * nc + c] = T(w[k]);
+                ndc[(size_t(lf) * 3 + k) * ns + c] = T(d[k]);
+                ggw[(size_t(lf) * 3 + k) * ns + c] = T(w[k]);
             }
         }
     }
@@ -1046,9 +1047,9 @@ void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
         for (int j = 0; j < n; ++j) perm[j] = j;
         std::sort(perm.begin(), perm.begin() + n, [&](int x, int y) { return ids[x] < ids[y]; });
         for (int j = 0; j < MC; ++j) {
-            sten_c[size_t(j) * nc + c] = j < n ? int32_t(ids[perm[j]]) : int32_t(c);
+            sten_c[size_t(j) * ns + c] = j < n ? int32_t(ids[perm[j]]) : int32_t(c);
             for (int k = 0; k < K; ++k)  // member-major rows: (j, k) at (j K + k) nc
-                Bc[(size_t(j) * K + k) * nc + c] = j < n ? T(m.Bc[(size_t(c) * K + k) * MC + perm[j]]) : T(0);
+                Bc[(size_t(j) * K + k) * ns + c] = j < n ? T(m.Bc[(size_t(c) * K + k) * MC + perm[j]]) : T(0);
         }
         ndir[c] = uint8_t(m.ndir[c]);
         for (int s = 0; s < ND; ++s) {
@@ -1057,33 +1058,32 @@ void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
             for (int j = 0; j < nd; ++j) perm[j] = j;
             std::sort(perm.begin(), perm.begin() + nd, [&](int x, int y) { return dids[x] < dids[y]; });
             for (int j = 0; j < MD; ++j) {
-                sten_d[(size_t(s) * MD + j) * nc + c] = j < nd ? int32_t(dids[perm[j]]) : int32_t(c);
+                sten_d[(size_t(s) * MD + j) * ns + c] = j < nd ? int32_t(dids[perm[j]]) : int32_t(c);
                 for (int k = 0; k < KD; ++k)  // member-major rows: (s, j, k) at ((s MD + j) kd + k) nc
-                    Bd[((size_t(s) * MD + j) * KD + k) * nc + c] =
+                    Bd[((size_t(s) * MD + j) * KD + k) * ns + c] =
                         j < nd ? T(m.Bd[((size_t(c) * m.nd_max + s) * KD + k) * m.md_pad + perm[j]]) : T(0);
             }
         }
         int t = 0;
-        if (m.order == 4)
+        if (reads_indicator_matrix(m.order, int(sizeof(T))))
             for (int k = 0; k < K; ++k)
-                for (int l = k; l < K; ++l) O[size_t(t++) * nc + c] = T(m.O[(size_t(c) * K + k) * K + l]);
-        const double h = m.hb[c];
-        th[c] = T(std::pow(m.vol[c], 2.0 / 3.0) / (h * h));
+                for (int l = k; l < K; ++l) O[size_t(t++) * ns + c] = T(m.O[(size_t(c) * K + k) * K + l]);
+        th[c] = T(m.O[size_t(c) * K * K]);  // the linear block is its first entry times the identity
         if (m.order == 3) {
             int r = 0;
             for (int i = 4; i >= 0; --i)
                 for (int j = 4 - i; j >= 0; --j)
-                    mom[size_t(r++) * nc + c] = T(m.moments[size_t(c) * m.nmom + mom_index(m.mom_deg, i, j, 4 - i - j)] /
-                                                  (m.vol[c] * std::pow(h, 4)));
+                    mom[size_t(r++) * ns + c] = T(m.moments[size_t(c) * m.nmom + mom_index(m.mom_deg, i, j, 4 - i - j)] /
+                                                  (m.vol[c] * std::pow(m.hb[c], 4)));
         }
-        for (int k = 0; k < K; ++k) pmean[size_t(k) * nc + c] = T(m.mean[size_t(c) * K + k]);
+        for (int k = 0; k < K; ++k) pmean[size_t(k) * ns + c] = T(m.mean[size_t(c) * K + k]);
         for (int lf = 0; lf < NF; ++lf) {
             const int32_t fs = m.c2f[c * kMaxFaces + lf];
-            c2f[size_t(lf) * nc + c] = fs;
-            cnq[size_t(lf) * nc + c] = fs >= 0 ? uint8_t(m.fnq[fs >> 1]) : 0;
+            c2f[size_t(lf) * ns + c] = fs;
+            cnq[size_t(lf) * ns + c] = fs >= 0 ? uint8_t(m.fnq[fs >> 1]) : 0;
             for (int q = 0; q < Q; ++q)
                 for (int d = 0; d < 3; ++d)
-                    xi[((size_t(lf) * Q + q) * 3 + d) * nc + c] = T(m.xi[((size_t(c) * NF + lf) * Q + q) * 3 + d]);
+                    xi[((size_t(lf) * Q + q) * 3 + d) * ns + c] = T(m.xi[((size_t(c) * NF + lf) * Q + q) * 3 + d]);
         }
         vol[c] = m.vol[c];
         hdt[c] = m.hdt[c];
@@ -1105,7 +1105,7 @@ void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
 
 int pack_arena(const Mesh& m, int precision, Arena& a, std::vector<unsigned char>* image) {
     const size_t ts = precision == UCNS_F32 ? 4 : 8;
-    const size_t nc = size_t(m.nc), nf = size_t(m.nf);
+    const size_t nc = size_t(m.nc), nf = size_t(m.nf), ns = size_t(m.ns);
     const size_t K = m.K, Q = m.qmax, NF = m.nfmax, MC = m.mc_pad, ND = std::max(1, m.nd_max),
                  MD = std::max(1, m.md_pad);
     size_t off = 0;
@@ -1114,18 +1114,18 @@ int pack_arena(const Mesh& m, int precision, Arena& a, std::vector<unsigned char
         off = align256(off + bytes);
         return o;
     };
-    a.sten_c = take(4 * MC * nc);
-    a.Bc = take(ts * K * MC * nc);
+    a.sten_c = take(4 * MC * ns);
+    a.Bc = take(ts * K * MC * ns);
     a.ndir = take(nc);
-    a.sten_d = take(4 * ND * MD * nc);
-    a.Bd = take(ts * ND * m.kd * MD * nc);
-    a.O = take(m.order == 4 ? ts * K * (K + 1) / 2 * nc : 0);
+    a.sten_d = take(4 * ND * MD * ns);
+    a.Bd = take(ts * ND * m.kd * MD * ns);
+    a.O = take(reads_indicator_matrix(m.order, int(ts)) ? ts * K * (K + 1) / 2 * ns : 0);
     a.th = take(ts * nc);
-    a.mom = take(ts * num_indicator_moments(m.order) * nc);
-    a.xi = take(ts * NF * Q * 3 * nc);
-    a.pmean = take(ts * K * nc);
-    a.c2f = take(4 * NF * nc);
-    a.cnq = take(NF * nc);
+    a.mom = take(ts * num_indicator_moments(m.order) * ns);
+    a.xi = take(ts * NF * Q * 3 * ns);
+    a.pmean = take(ts * K * ns);
+    a.c2f = take(4 * NF * ns);
+    a.cnq = take(NF * ns);
     a.vol = take(8 * nc);
     a.hdt = take(8 * nc);
     a.fcell = take(8 * nf);
@@ -1135,12 +1135,12 @@ int pack_arena(const Mesh& m, int precision, Arena& a, std::vector<unsigned char
     a.fw = take(ts * Q * nf);
     a.fdc = take(ts * 3 * nf);
     a.fnq = take(nf);
-    a.nbr = take(4 * NF * nc);
-    a.ndc = take(ts * NF * 3 * nc);
+    a.nbr = take(4 * NF * ns);
+    a.ndc = take(ts * NF * 3 * ns);
     a.hb = take(ts * nc);
     a.ncen = take(nc);
-    a.glsq = take(ts * NF * 3 * nc);
-    a.ggw = take(ts * NF * 3 * nc);
+    a.glsq = take(ts * NF * 3 * ns);
+    a.ggw = take(ts * NF * 3 * ns);
     a.ustage = take(m.order == 4 ? 64 * nc : 0);  // scratch, written per reconstruction call
     a.bytes = off;
     if (image) {

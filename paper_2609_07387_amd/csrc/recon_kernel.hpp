@@ -25,11 +25,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base, uint64_
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0,
                                              int(bytes < 0xffffffffull ? uint32_t(bytes) : 0xffffffffu), 0x00020000);
 }
-// Descriptor of `rows` rows of n_cell entries starting at row `row` of a
-// cell-fastest array (64-bit base arithmetic in scalar registers).
+// Descriptor of `rows` rows starting at row `row` of a cell-fastest array
+// with `stride` entries per row (64-bit base arithmetic in scalar registers).
 template <class E>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const E* base, int64_t row, int64_t nc, int rows = 1) {
-    return rsrc(base + row * nc, uint64_t(rows) * uint64_t(nc) * sizeof(E));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const E* base, int64_t row, int64_t stride, int rows = 1) {
+    return rsrc(base + row * stride, uint64_t(rows) * uint64_t(stride) * sizeof(E));
 }
 template <class T>
 __device__ __forceinline__ T bld(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) {
@@ -37,6 +37,16 @@ __device__ __forceinline__ T bld(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint3
         return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(rs, int(voff), int(soff), 0));
     else
         return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rs, int(voff), int(soff), 0));
+}
+// bld of a stream that the call reads once (operators, stencil ids, face
+// points); NT marks it non-temporal (the choice: nt_streams).
+template <class T, bool NT>
+__device__ __forceinline__ T blds(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) {
+    constexpr int kAux = NT ? 2 : 0;
+    if constexpr (sizeof(T) == 4)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(rs, int(voff), int(soff), kAux));
+    else
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rs, int(voff), int(soff), kAux));
 }
 // f(integral_constant<int, I>) for I = 0 .. N-1, unrolled at compile time
 template <int I, int N, class F>
@@ -47,12 +57,12 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-template <class T>
+template <class T, int AUX = 0>
 __device__ __forceinline__ void bst(T val, __amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) {
     if constexpr (sizeof(T) == 4)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, val), rs, int(voff), int(soff), 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, val), rs, int(voff), int(soff), AUX);
     else
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, val), rs, int(voff), int(soff), 0);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, val), rs, int(voff), int(soff), AUX);
 }
 
 // a = B_c b over the central stencil.  With FEAT, js[] also receives the max
@@ -62,16 +72,16 @@ __device__ __forceinline__ void bst(T val, __amdgpu_buffer_rsrc_t rs, uint32_t v
 // MCw (wave-uniform, at most MC) bounds the member loop: the largest central
 // stencil among the wave's cells (slots past a cell's own stencil hold zero
 // operator rows and the cell itself, so they add nothing).
-template <class T, int K, bool FEAT = false>
+template <class T, int K, bool FEAT = false, bool NT = false>
 __device__ __forceinline__ void central_coeffs(const ReconArgs<T>& A, int64_t c, const double* ui, T a[K][5],
                                                T* js = nullptr, int MCw = 0) {
-    const int64_t nc = A.nc;
+    const int64_t nc = A.nc, ns = A.ns;
     const int MC = MCw > 0 && MCw < A.MC ? MCw : A.MC;
     // member m's id at sten_c[m][c]; its K operator rows at Bc[m][k][c]; U[v][j]
-    const uint32_t rowT = uint32_t(nc) * uint32_t(sizeof(T)), rowU = uint32_t(nc) * 8u;
+    const uint32_t rowT = uint32_t(ns) * uint32_t(sizeof(T)), rowU = uint32_t(nc) * 8u;
     const uint32_t c4 = uint32_t(c) * 4u, cT = uint32_t(c) * uint32_t(sizeof(T));
     const auto rU = rsrc(A.U, uint64_t(5) * rowU);
-    auto member_id = [&](int m) { return bld<int32_t>(row_rsrc(A.sten_c, m, nc), c4, 0u); };
+    auto member_id = [&](int m) { return blds<int32_t, NT>(row_rsrc(A.sten_c, m, ns), c4, 0u); };
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
@@ -96,9 +106,9 @@ __device__ __forceinline__ void central_coeffs(const ReconArgs<T>& A, int64_t c,
         auto load_member = [&](int m, int32_t j, double* uu, T* bb) {
 #pragma unroll
             for (int v = 0; v < 5; ++v) uu[v] = bld<double>(rU, uint32_t(j) * 8u, uint32_t(v) * rowU);
-            const auto rB = row_rsrc(A.Bc, int64_t(last(m)) * K, nc, K);
+            const auto rB = row_rsrc(A.Bc, int64_t(last(m)) * K, ns, K);
 #pragma unroll
-            for (int k = 0; k < K; ++k) bb[k] = bld<T>(rB, cT, uint32_t(k) * rowT);
+            for (int k = 0; k < K; ++k) bb[k] = blds<T, NT>(rB, cT, uint32_t(k) * rowT);
         };
 #pragma unroll
         for (int d = 0; d < DEPTH + R; ++d) {
@@ -153,9 +163,9 @@ __device__ __forceinline__ void central_coeffs(const ReconArgs<T>& A, int64_t c,
         for (int d = 0; d < DEPTH; ++d) {
 #pragma unroll
             for (int v = 0; v < 5; ++v) u[d][v] = bld<double>(rU, uint32_t(jn[d]) * 8u, uint32_t(v) * rowU);
-            const auto rB = row_rsrc(A.Bc, int64_t(last(d)) * K, nc, K);
+            const auto rB = row_rsrc(A.Bc, int64_t(last(d)) * K, ns, K);
 #pragma unroll
-            for (int k = 0; k < K; ++k) b[d][k] = bld<T>(rB, cT, uint32_t(k) * rowT);
+            for (int k = 0; k < K; ++k) b[d][k] = blds<T, NT>(rB, cT, uint32_t(k) * rowT);
         }
         int32_t jnext = jn[DEPTH];  // id of member DEPTH
 #pragma unroll DEPTH + 1
@@ -166,9 +176,9 @@ __device__ __forceinline__ void central_coeffs(const ReconArgs<T>& A, int64_t c,
 #pragma unroll
             for (int v = 0; v < 5; ++v) u[DEPTH][v] = bld<double>(rU, uint32_t(jnext) * 8u, uint32_t(v) * rowU);
             {
-                const auto rB = row_rsrc(A.Bc, int64_t(mf) * K, nc, K);
+                const auto rB = row_rsrc(A.Bc, int64_t(mf) * K, ns, K);
 #pragma unroll
-                for (int k = 0; k < K; ++k) b[DEPTH][k] = bld<T>(rB, cT, uint32_t(k) * rowT);
+                for (int k = 0; k < K; ++k) b[DEPTH][k] = blds<T, NT>(rB, cT, uint32_t(k) * rowT);
             }
             // member m
             T bv[5];
@@ -223,10 +233,10 @@ __device__ __forceinline__ T feat_log(T x) {
         return log(x);
 }
 
-template <class T, int K>
+template <class T, int K, bool NT = false>
 __device__ __forceinline__ void gate_features(const ReconArgs<T>& A, int64_t c, const double* ui, const T a[K][5],
                                               const T* js, float* f) {
-    const int64_t nc = A.nc;
+    const int64_t nc = A.nc, ns = A.ns;
     const T h = A.hb[c], ninv = T(1) / T(A.ncen[c]);
     T au[2], g[2][3], gn[2], dmax[2], dsum[2], dmin[2];
 #pragma unroll
@@ -242,7 +252,7 @@ __device__ __forceinline__ void gate_features(const ReconArgs<T>& A, int64_t c, 
     // one pass over the face neighbours for both variables; all their ids,
     // offsets and states are loaded up front (two memory round trips in all)
     const int NF = A.NF;
-    const uint32_t rowI = uint32_t(nc) * 4u, rowT = uint32_t(nc) * uint32_t(sizeof(T)), rowU = uint32_t(nc) * 8u;
+    const uint32_t rowI = uint32_t(ns) * 4u, rowT = uint32_t(ns) * uint32_t(sizeof(T)), rowU = uint32_t(nc) * 8u;
     const uint32_t c4 = uint32_t(c) * 4u, cT = uint32_t(c) * uint32_t(sizeof(T));
     const auto rN = rsrc(A.nbr, uint64_t(NF) * rowI);
     const auto rU = rsrc(A.U, uint64_t(5) * rowU);
@@ -251,10 +261,10 @@ __device__ __forceinline__ void gate_features(const ReconArgs<T>& A, int64_t c, 
     double un[kMaxFaces][2];
 #pragma unroll
     for (int lf = 0; lf < kMaxFaces; ++lf) {
-        jn[lf] = lf < NF ? bld<int32_t>(rN, c4, uint32_t(lf) * rowI) : -1;
+        jn[lf] = lf < NF ? blds<int32_t, NT>(rN, c4, uint32_t(lf) * rowI) : -1;
 #pragma unroll
         for (int d = 0; d < 3; ++d)
-            dn[lf][d] = lf < NF ? bld<T>(row_rsrc(A.ndc, int64_t(lf) * 3, nc, 3), cT, uint32_t(d) * rowT) : T(0);
+            dn[lf][d] = lf < NF ? blds<T, NT>(row_rsrc(A.ndc, int64_t(lf) * 3, ns, 3), cT, uint32_t(d) * rowT) : T(0);
     }
 #pragma unroll
     for (int lf = 0; lf < kMaxFaces; ++lf)
@@ -323,6 +333,33 @@ struct MonoTable {
 constexpr MonoTable kMono{};
 constexpr int mono_at(int i, int j, int k) { return i + j + k == 0 ? -1 : kMono.at[i][j][k]; }
 
+// SI_1 = a^T O a with O stored as its upper triangle (FP32 P2: the formula
+// below rounds the indicators differently, and through the nonlinear weights
+// a run's FP64 state by more than 1e-9 of itself, for 2 % of a call's time).
+template <class T, int K>
+__device__ __forceinline__ void si_matrix(const ReconArgs<T>& A, int64_t c, const T a[K][5], T SI1[5]) {
+    const int64_t ns = A.ns;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) SI1[v] = T(0);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const T okk = A.O[int64_t(tri_index(K, k, k)) * ns + c];
+        T t[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) t[v] = okk * a[k][v];
+#pragma unroll
+        for (int l = k + 1; l < K; ++l) {
+            const T o2 = T(2) * A.O[int64_t(tri_index(K, k, l)) * ns + c];
+#pragma unroll
+            for (int v = 0; v < 5; ++v) t[v] += o2 * a[l][v];
+        }
+#pragma unroll
+        for (int v = 0; v < 5; ++v) SI1[v] += a[k][v] * t[v];
+    }
+#pragma unroll
+    for (int v = 0; v < 5; ++v) SI1[v] = fmax(SI1[v], T(0));
+}
+
 // SI_1 per variable: the quadratic form a^T O a of the indicator matrix
 // O_kl = sum_{1<=|b|<=r} V^(2|b|/3 - 1) int D^b phi_k D^b phi_l, evaluated as
 // what it is, sum_b theta^|b| mean((D^b p)^2) with theta = V^(2/3)/h^2 and
@@ -332,19 +369,23 @@ constexpr int mono_at(int i, int j, int k) { return i + j + k == 0 ? -1 : kMono.
 // first moments about the centroid vanish), so a cell reads 7 (P2) or 32
 // (P3) values instead of O's 45 or 190 entries, at about as many
 // multiply-adds.  The calls are bound by HBM, so the bytes are what counts:
-// FP64 64^3 hex P2 call 332 -> 312 us, 196,608 P3 tets 443 -> 404 us, gated
-// FP32 shocked tets 215 -> 204 us.
+// FP64 64^3 hex P2 call 332 -> 312 us, 196,608 P3 tets FP64 443 -> 404 us,
+// 44,574 FP32 65.4 -> 61.9 us.
 template <class T, int K>
 __device__ __forceinline__ void si_opt(const ReconArgs<T>& A, int64_t c, const T a[K][5], T SI1[5]) {
     static_assert(K == 9 || K == 19);
+    if constexpr (K == 9 && sizeof(T) == 4) {
+        si_matrix<T, K>(A, c, a, SI1);
+        return;
+    }
     constexpr int R = K == 9 ? 2 : 3;         // degree
     constexpr int ND = R == 2 ? 4 : 10;       // coefficients of a first derivative (degree R - 1)
     constexpr int NM = R == 2 ? 9 : 34;       // moments of degree 1 .. 2 R - 2
-    const int64_t nc = A.nc;
+    const int64_t ns = A.ns;
     const T th = A.th[c];
     T M[NM];
-    static_for<3, K>([&](auto k) { M[k] = A.pmean[int64_t(k) * nc + c]; });
-    if constexpr (R == 3) static_for<K, NM>([&](auto k) { M[k] = A.mom[int64_t(k - K) * nc + c]; });
+    static_for<3, K>([&](auto k) { M[k] = A.pmean[int64_t(k) * ns + c]; });
+    if constexpr (R == 3) static_for<K, NM>([&](auto k) { M[k] = A.mom[int64_t(k - K) * ns + c]; });
     // entry (i, j) of the moment matrix of (1, monomials); -1 stands for 1
     auto mean = [&](auto I, auto J) -> T {
         constexpr int i = decltype(I)::value - 1, j = decltype(J)::value - 1;
@@ -469,12 +510,12 @@ constexpr int stage_points() { return face_qmax<K>() <= 4 ? face_qmax<K>() : 3; 
 // stores; a lane without the point stores a value into its unused slot.
 // Otherwise (the positivity fallback, the mesh's last, partial wave) each
 // lane stores its own points' five values.
-template <class T, int K, bool STAGE>
+template <class T, int K, bool STAGE, bool NT>
 __device__ __forceinline__ bool face_values(const ReconArgs<T>& A, int64_t c, const double* ui, int mode,
                                             const T a[K][5], T* stage = nullptr) {
-    const int64_t nc = A.nc;
+    const int64_t nc = A.nc, ns = A.ns;
     const int NF = A.NF, Q = A.Q;
-    const uint32_t rowT = uint32_t(nc) * uint32_t(sizeof(T));
+    const uint32_t rowT = uint32_t(ns) * uint32_t(sizeof(T));
     const uint32_t cT = uint32_t(c) * uint32_t(sizeof(T));
     const int64_t ncp = fs_cells_padded(nc);
     const int lane = int(threadIdx.x & 63u);
@@ -485,7 +526,7 @@ __device__ __forceinline__ bool face_values(const ReconArgs<T>& A, int64_t c, co
     const bool staged = STAGE && c - lane + 64 <= nc;  // wave-uniform
     T pm[K];
     {
-        const auto rM = row_rsrc(A.pmean, 0, nc, K);
+        const auto rM = row_rsrc(A.pmean, 0, ns, K);
 #pragma unroll
         for (int k = 0; k < K; ++k) pm[k] = bld<T>(rM, cT, uint32_t(k) * rowT);
     }
@@ -499,11 +540,11 @@ __device__ __forceinline__ bool face_values(const ReconArgs<T>& A, int64_t c, co
     auto load_face = [&](int lf, T (&x)[QM][3]) {
 #pragma unroll
         for (int q = 0; q < QM; ++q) {
-            const auto rX = row_rsrc(A.xi, (int64_t(lf) * Q + q) * 3, nc, 3);
+            const auto rX = row_rsrc(A.xi, (int64_t(lf) * Q + q) * 3, ns, 3);
 #pragma unroll
-            for (int d = 0; d < 3; ++d) x[q][d] = q < Q ? bld<T>(rX, cT, uint32_t(d) * rowT) : T(0);
+            for (int d = 0; d < 3; ++d) x[q][d] = q < Q ? blds<T, NT>(rX, cT, uint32_t(d) * rowT) : T(0);
         }
-        return int(__builtin_amdgcn_raw_buffer_load_b8(row_rsrc(A.cnq, lf, nc), int(uint32_t(c)), 0, 0));
+        return int(__builtin_amdgcn_raw_buffer_load_b8(row_rsrc(A.cnq, lf, ns), int(uint32_t(c)), 0, 0));
     };
     T x[QM][3], xn[QM][3];
     int nq = load_face(0, x);
@@ -537,13 +578,20 @@ __device__ __forceinline__ bool face_values(const ReconArgs<T>& A, int64_t c, co
                 for (int v = 0; v < 5; ++v) stage[sq * 320 + lane * 5 + v] = val[v];
                 if (sq == QB - 1 || q == Q - 1) {  // wave-uniform: flush the batch
                     __builtin_amdgcn_wave_barrier();
+                    auto flush = [&](auto aux) {
 #pragma unroll
-                    for (int b = 0; b <= sq; ++b) {
-                        const auto rF = row_rsrc(A.fs, (int64_t(lf) * Q + q - sq + b) * 5, ncp, 5);
+                        for (int b = 0; b <= sq; ++b) {
+                            const auto rF = row_rsrc(A.fs, (int64_t(lf) * Q + q - sq + b) * 5, ncp, 5);
 #pragma unroll
-                        for (int k = 0; k < 5; ++k)
-                            bst<T>(stage[b * 320 + k * 64 + lane], rF, wF, uint32_t(k) * 64u * uint32_t(sizeof(T)));
-                    }
+                            for (int k = 0; k < 5; ++k)
+                                bst<T, decltype(aux)::value>(stage[b * 320 + k * 64 + lane], rF, wF,
+                                                             uint32_t(k) * 64u * uint32_t(sizeof(T)));
+                        }
+                    };
+                    if (A.fs_nt)
+                        flush(std::integral_constant<int, 2>{});
+                    else
+                        flush(std::integral_constant<int, 0>{});
                     __builtin_amdgcn_wave_barrier();
                 }
             } else {
@@ -596,7 +644,7 @@ __device__ __forceinline__ void blend_add(const ReconArgs<T>& A, Blend<T>& B, co
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
         const T x = as[0][v], y = as[1][v], z = as[2][v];
-        const T SIs = fmax(B.th * (x * x + y * y + z * z), T(0));
+        const T SIs = fmax(x * (B.th * x) + y * (B.th * y) + z * B.th * z, T(0));
         B.tsum[v] += fabs(B.SI1[v] - SIs);
         const T r = T(1) / (A.eps + SIs);
         B.Lam[v] += B.lam_s * r;
@@ -638,10 +686,10 @@ __device__ __forceinline__ void blend_finish(Blend<T>& B, int nd, float& lab, T 
 // One lane per cell: steps (iii)-(vi) for a cell with nd > 0 directional
 // stencils.  a holds the central coefficients on entry; it is overwritten by
 // the blend.
-template <class T, int K, bool LABEL>
+template <class T, int K, bool LABEL, bool NT>
 __device__ __forceinline__ void dir_blend_lane(const ReconArgs<T>& A, int64_t c, const double* ui, int nd, float& lab,
                                                T a[K][5]) {
-    const int64_t nc = A.nc;
+    const int64_t nc = A.nc, ns = A.ns;
     Blend<T> B;
     blend_init<T, K>(A, c, nd, a, B);
     // all directional members as one pipelined stream t = s * MD + m over
@@ -649,11 +697,11 @@ __device__ __forceinline__ void dir_blend_lane(const ReconArgs<T>& A, int64_t c,
     // nd hold zero operators and are not counted); the id of member t at
     // sten_d[t][c], its 3 operator rows at Bd[t][k][c]
     const int MD = A.MD, total = A.ND * MD;
-    const uint32_t rowT = uint32_t(nc) * uint32_t(sizeof(T));
+    const uint32_t rowT = uint32_t(ns) * uint32_t(sizeof(T));
     const uint32_t rowU = uint32_t(nc) * 8u;
     const uint32_t c4 = uint32_t(c) * 4u, cT = uint32_t(c) * uint32_t(sizeof(T));
     const auto rU = rsrc(A.U, uint64_t(5) * rowU);
-    auto member_id = [&](int t) { return bld<int32_t>(row_rsrc(A.sten_d, t, nc), c4, 0u); };
+    auto member_id = [&](int t) { return blds<int32_t, NT>(row_rsrc(A.sten_d, t, ns), c4, 0u); };
     if constexpr (K <= 9) {
         // loads DEPTH members ahead and ids R = DEPTH + 1 further, in trips of R
         // members with compile-time slots, as in central_coeffs
@@ -666,9 +714,9 @@ __device__ __forceinline__ void dir_blend_lane(const ReconArgs<T>& A, int64_t c,
         auto load_member = [&](int t, int32_t j, double* uu, T* bb) {
 #pragma unroll
             for (int v = 0; v < 5; ++v) uu[v] = bld<double>(rU, uint32_t(j) * 8u, uint32_t(v) * rowU);
-            const auto rB = row_rsrc(A.Bd, int64_t(last(t)) * 3, nc, 3);
+            const auto rB = row_rsrc(A.Bd, int64_t(last(t)) * 3, ns, 3);
 #pragma unroll
-            for (int k = 0; k < 3; ++k) bb[k] = bld<T>(rB, cT, uint32_t(k) * rowT);
+            for (int k = 0; k < 3; ++k) bb[k] = blds<T, NT>(rB, cT, uint32_t(k) * rowT);
         };
 #pragma unroll
         for (int d = 0; d < DEPTH + R; ++d) {
@@ -730,9 +778,9 @@ __device__ __forceinline__ void dir_blend_lane(const ReconArgs<T>& A, int64_t c,
         for (int d = 0; d < DEPTH; ++d) {
 #pragma unroll
             for (int v = 0; v < 5; ++v) u[d][v] = bld<double>(rU, uint32_t(jn[d]) * 8u, uint32_t(v) * rowU);
-            const auto rB = row_rsrc(A.Bd, int64_t(last(d)) * 3, nc, 3);
+            const auto rB = row_rsrc(A.Bd, int64_t(last(d)) * 3, ns, 3);
 #pragma unroll
-            for (int k = 0; k < 3; ++k) b[d][k] = bld<T>(rB, cT, uint32_t(k) * rowT);
+            for (int k = 0; k < 3; ++k) b[d][k] = blds<T, NT>(rB, cT, uint32_t(k) * rowT);
         }
         int32_t jnext = jn[DEPTH];
         T as[3][5];
@@ -748,9 +796,9 @@ __device__ __forceinline__ void dir_blend_lane(const ReconArgs<T>& A, int64_t c,
 #pragma unroll
             for (int v = 0; v < 5; ++v) u[DEPTH][v] = bld<double>(rU, uint32_t(jnext) * 8u, uint32_t(v) * rowU);
             {
-                const auto rB = row_rsrc(A.Bd, int64_t(tf) * 3, nc, 3);
+                const auto rB = row_rsrc(A.Bd, int64_t(tf) * 3, ns, 3);
 #pragma unroll
-                for (int k = 0; k < 3; ++k) b[DEPTH][k] = bld<T>(rB, cT, uint32_t(k) * rowT);
+                for (int k = 0; k < 3; ++k) b[DEPTH][k] = blds<T, NT>(rB, cT, uint32_t(k) * rowT);
             }
             T bv[5];
 #pragma unroll
@@ -827,7 +875,7 @@ constexpr int kWaveBlendMax = 2;
 template <class T, int K>
 __device__ __forceinline__ void dir_blend_wave(const ReconArgs<T>& A, uint64_t todo, int64_t c, const double* ui,
                                                int nd, T a[K][5]) {
-    const int64_t nc = A.nc;
+    const int64_t nc = A.nc, ns = A.ns;
     const int lane = int(threadIdx.x & 63u);
     const int MD = A.MD, total = A.ND * MD, m = lane % MD;
     const bool mine = (todo >> lane) & 1u;
@@ -844,10 +892,10 @@ __device__ __forceinline__ void dir_blend_wave(const ReconArgs<T>& A, uint64_t t
 #pragma unroll
             for (int v = 0; v < 5; ++v) x[k][v] = T(0);
         if (lane < total) {
-            const int32_t j = A.sten_d[int64_t(lane) * nc + cL];
+            const int32_t j = A.sten_d[int64_t(lane) * ns + cL];
             T b[3];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) b[k] = A.Bd[(int64_t(lane) * 3 + k) * nc + cL];
+            for (int k = 0; k < 3; ++k) b[k] = A.Bd[(int64_t(lane) * 3 + k) * ns + cL];
 #pragma unroll
             for (int v = 0; v < 5; ++v) {
                 const T bv = T(A.U[v * nc + j] - lane_read(ui[v], L));
@@ -911,7 +959,7 @@ template <int K, int SDEPTH = 2>
 __device__ __forceinline__ void dir_blend_stencils(const ReconArgs<float>& A, uint64_t todo, int64_t c,
                                                    const double* ui, int nd, float a[K][5], float* stash) {
     using T = float;
-    const int64_t nc = A.nc;
+    const int64_t nc = A.nc, ns = A.ns;
     const int lane = int(threadIdx.x & 63u);
     const int ND = A.ND, MD = A.MD, per = 64 / ND;
     const int p = lane / ND, s = lane - p * ND;  // this lane's cell (within the pass) and stencil
@@ -954,22 +1002,22 @@ __device__ __forceinline__ void dir_blend_stencils(const ReconArgs<float>& A, ui
             T b[SDEPTH + 1][3];
             int32_t jn[SDEPTH + 1];
 #pragma unroll
-            for (int d = 0; d <= SDEPTH; ++d) jn[d] = A.sten_d[row(d) * nc + cq];
+            for (int d = 0; d <= SDEPTH; ++d) jn[d] = A.sten_d[row(d) * ns + cq];
 #pragma unroll
             for (int d = 0; d < SDEPTH; ++d) {
 #pragma unroll
                 for (int v = 0; v < 5; ++v) u[d][v] = A.U[v * nc + jn[d]];
 #pragma unroll
-                for (int k = 0; k < 3; ++k) b[d][k] = A.Bd[(row(d) * 3 + k) * nc + cq];
+                for (int k = 0; k < 3; ++k) b[d][k] = A.Bd[(row(d) * 3 + k) * ns + cq];
             }
             int32_t jnext = jn[SDEPTH];
 #pragma unroll 1
             for (int m = 0; m < MD; ++m) {
-                const int32_t jf = A.sten_d[row(m + SDEPTH + 1) * nc + cq];
+                const int32_t jf = A.sten_d[row(m + SDEPTH + 1) * ns + cq];
 #pragma unroll
                 for (int v = 0; v < 5; ++v) u[SDEPTH][v] = A.U[v * nc + jnext];
 #pragma unroll
-                for (int k = 0; k < 3; ++k) b[SDEPTH][k] = A.Bd[(row(m + SDEPTH) * 3 + k) * nc + cq];
+                for (int k = 0; k < 3; ++k) b[SDEPTH][k] = A.Bd[(row(m + SDEPTH) * 3 + k) * ns + cq];
 #pragma unroll
                 for (int v = 0; v < 5; ++v) {
                     const T bv = T(u[0][v] - up[v]);
@@ -1006,7 +1054,7 @@ __device__ __forceinline__ void dir_blend_stencils(const ReconArgs<float>& A, ui
 #pragma unroll
             for (int v = 0; v < 5; ++v) {
                 const T x = as[0][v], y = as[1][v], z = as[2][v];
-                const T SIs = fmax(th * (x * x + y * y + z * z), T(0));
+                const T SIs = fmax(x * (th * x) + y * (th * y) + z * th * z, T(0));
                 ts[v] = fabs(SI1p[v] - SIs);
                 const T r = T(1) / (A.eps + SIs);
                 lm[v] = lam_s * r;
@@ -1061,14 +1109,14 @@ __device__ __forceinline__ void dir_blend_stencils(const ReconArgs<float>& A, ui
 // One lane per cell: steps (iii)-(vi) for mode 1, then (vii) for any mode
 // (STAGE: the main pass; the positivity fallback runs on scattered cells and
 // stores its own points).
-template <class T, int K, bool LABEL, bool STAGE = false>
+template <class T, int K, bool LABEL, bool STAGE = false, bool NT = false>
 __device__ __forceinline__ bool recon_cell(const ReconArgs<T>& A, int64_t c, const double* ui, int mode, float& lab,
                                            T a[K][5], T* stage = nullptr) {
     if (mode == 1) {
         const int nd = A.ndir[c];
-        if (nd > 0) dir_blend_lane<T, K, LABEL>(A, c, ui, nd, lab, a);
+        if (nd > 0) dir_blend_lane<T, K, LABEL, NT>(A, c, ui, nd, lab, a);
     }
-    return face_values<T, K, STAGE>(A, c, ui, mode, a, stage);
+    return face_values<T, K, STAGE, NT>(A, c, ui, mode, a, stage);
 }
 
 // Main pass without a gate (full CWENOZ everywhere), or with a gate (a mask,
@@ -1091,7 +1139,7 @@ __device__ __forceinline__ bool recon_cell(const ReconArgs<T>& A, int64_t c, con
 // flag for the fallback pass.  GRAD (1 Green-Gauss, 2 least squares): the
 // cell then forms its gradient of W as well (the positivity fallback changes
 // point states only, never the cell averages the gradient is taken from).
-template <class T, int K, bool LABEL, bool GATE, int GRAD = 0>
+template <class T, int K, bool LABEL, bool GATE, int GRAD, bool NT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     K == 9 && (sizeof(T) == 4 ? GATE : !GATE && !LABEL) ? (sizeof(T) == 4 ? 3 : 2) : 1)))
 void reconstruct_kernel(ReconArgs<T> A) {
@@ -1119,8 +1167,8 @@ void reconstruct_kernel(ReconArgs<T> A) {
 #pragma unroll
                 for (int v = 0; v < 5; ++v) ui[v] = A.U[v * A.nc + c];
                 T js[4];
-                central_coeffs<T, K, true>(A, c, ui, a, js, MCw);
-                gate_features<T, K>(A, c, ui, a, js, f);
+                central_coeffs<T, K, true, NT>(A, c, ui, a, js, MCw);
+                gate_features<T, K, NT>(A, c, ui, a, js, f);
             } else {
 #pragma unroll
                 for (int k = 0; k < 12; ++k) f[k] = fv[mlpimg::kMu + k];
@@ -1130,7 +1178,7 @@ void reconstruct_kernel(ReconArgs<T> A) {
         } else if (valid) {
 #pragma unroll
             for (int v = 0; v < 5; ++v) ui[v] = A.U[v * A.nc + c];
-            central_coeffs<T, K>(A, c, ui, a, nullptr, MCw);
+            central_coeffs<T, K, false, NT>(A, c, ui, a, nullptr, MCw);
             mode = A.gate[c] ? 0 : 1;
         }
         // troubled cells: the whole wave per cell when the wave has few, one
@@ -1151,25 +1199,25 @@ void reconstruct_kernel(ReconArgs<T> A) {
         }
         if (!done && nd > 0) {
             float lab = 0.f;
-            dir_blend_lane<T, K, false>(A, c, ui, nd, lab, a);
+            dir_blend_lane<T, K, false, NT>(A, c, ui, nd, lab, a);
         }
         if (!valid) return;
         if (A.mask_out) A.mask_out[c] = mode == 0 ? 1 : 0;
         // the network's LDS row is free again: it stages the point states
-        const bool ok = face_values<T, K, true>(A, c, ui, 0, a, reinterpret_cast<T*>(wl));
+        const bool ok = face_values<T, K, true, NT>(A, c, ui, 0, a, reinterpret_cast<T*>(wl));
         A.flags[c] = uint8_t((mode == 0 ? 1 : 0) | (ok ? 0 : 0x80));
-        if constexpr (GRAD != 0) cell_gradient<T, GRAD == 2>(A, c, ui);
+        if constexpr (GRAD != 0) cell_gradient<T, GRAD == 2, NT>(A, c, ui);
     } else {
         __shared__ T stage[kBlock / 64][stage_points<K>() * 320];
         if (!valid) return;
 #pragma unroll
         for (int v = 0; v < 5; ++v) ui[v] = A.U[v * A.nc + c];
-        central_coeffs<T, K>(A, c, ui, a, nullptr, MCw);
+        central_coeffs<T, K, false, NT>(A, c, ui, a, nullptr, MCw);
         float lab = 0.f;
-        const bool ok = recon_cell<T, K, LABEL, true>(A, c, ui, 1, lab, a, stage[threadIdx.x >> 6]);
+        const bool ok = recon_cell<T, K, LABEL, true, NT>(A, c, ui, 1, lab, a, stage[threadIdx.x >> 6]);
         A.flags[c] = uint8_t(ok ? 0 : 0x80);
         if constexpr (LABEL) A.label[c] = lab;
-        if constexpr (GRAD != 0) cell_gradient<T, GRAD == 2>(A, c, ui);
+        if constexpr (GRAD != 0) cell_gradient<T, GRAD == 2, NT>(A, c, ui);
     }
 }
 

@@ -272,7 +272,7 @@ template <class T, bool LABEL>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? kP4Waves32 : kP4Waves64)))
 void reconstruct_p4_kernel(ReconArgs<T> A) {
     constexpr int K = kP4K, KD = kP4KD, NT = kP4T, NTD = kP4TD;
-    const int64_t nc = A.nc;
+    const int64_t nc = A.nc, ns = A.ns;
     const int lane = int(threadIdx.x & 63u);
     const int slot = lane >> 2, h = lane & 3;
     const int64_t c0 = (xcd_block() * (kBlock / 64) + int64_t(threadIdx.x >> 6)) * kP4Cells;
@@ -286,7 +286,7 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
     // descriptor, the lane's byte offset in a 32-bit register (the launcher
     // bounds every such span below 4 GiB).
     const uint32_t cT = uint32_t(c) * uint32_t(sizeof(T)), c4 = uint32_t(c) * 4u;
-    const uint32_t rowT = uint32_t(nc) * uint32_t(sizeof(T));
+    const uint32_t rowT = uint32_t(ns) * uint32_t(sizeof(T));
     const auto rS = rsrc(A.ustage, uint64_t(nc) * 64u);  // the staged [cell][8] state
     const uint32_t hofs = uint32_t(h) * 8u;              // the lane's variable in a cell's record
     // operator rows of the lane's terms (padding terms read the last row),
@@ -308,7 +308,7 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
     for (int v = 0; v < 5; ++v)
 #pragma unroll
         for (int i = 0; i < NT; ++i) a[v][i] = T(0);
-    p4_stream<T, NT, sizeof(T) == 4 ? kP4OpAhead32 : kP4OpAhead64>(A.sten_c, A.Bc, K, A.MC, nc, c4, toff, rS, hofs, ui, h,
+    p4_stream<T, NT, sizeof(T) == 4 ? kP4OpAhead32 : kP4OpAhead64>(A.sten_c, A.Bc, K, A.MC, ns, c4, toff, rS, hofs, ui, h,
                                              [&](int, const T* bv, const T* b) {
 #pragma unroll
                                                  for (int v = 0; v < 5; ++v)
@@ -322,7 +322,7 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
 
     // (iii) SI_1 = a^T O a
     T SI1[5];
-    p4_forms<T, NT>(A.O, nc, c, h, tbase, a, SI1);
+    p4_forms<T, NT>(A.O, ns, c, h, tbase, a, SI1);
     // the terms of degree 3 and 4 (i >= 3) take no part in the directional
     // step: parked in LDS (each lane its own slots) until the blend
     __shared__ T park[kBlock / 64][5 * (NT - NTD)][64];
@@ -361,8 +361,8 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
             for (int v = 0; v < 5; ++v)
 #pragma unroll
                 for (int i = 0; i < NTD; ++i) as[v][i] = T(0);
-            p4_stream<T, NTD, sizeof(T) == 4 ? kP4OpAhead32 : kP4OpAhead64>(A.sten_d + int64_t(s) * MD * nc, A.Bd + int64_t(s) * MD * KD * nc,
-                                                      KD, MD, nc, c4, doff, rS, hofs, ui, h,
+            p4_stream<T, NTD, sizeof(T) == 4 ? kP4OpAhead32 : kP4OpAhead64>(A.sten_d + int64_t(s) * MD * ns, A.Bd + int64_t(s) * MD * KD * ns,
+                                                      KD, MD, ns, c4, doff, rS, hofs, ui, h,
                                                       [&](int, const T* bv, const T* b) {
 #pragma unroll
                                                           for (int v = 0; v < 5; ++v)
@@ -376,7 +376,7 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
             if (s < nd) {
                 // SI_s with the block of O on the first KD terms
                 T SIs[5];
-                p4_forms<T, NTD>(A.O, nc, c, h, tbase, as, SIs);
+                p4_forms<T, NTD>(A.O, ns, c, h, tbase, as, SIs);
 #pragma unroll
                 for (int v = 0; v < 5; ++v) {
                     tsum[v] += fabs(SI1[v] - SIs[v]);
@@ -425,7 +425,7 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
     // lane h writes variable h, lane 0 also variable 4
     T pm[NT];
 #pragma unroll
-    for (int i = 0; i < NT; ++i) pm[i] = A.pmean[int64_t(trow[i]) * nc + c];
+    for (int i = 0; i < NT; ++i) pm[i] = A.pmean[int64_t(trow[i]) * ns + c];
     bool ok = true;
     // The face points as one sequence p = lf Q + q, in trips of 8 points.
     // Offsets load four points per instruction (lane h of the quad takes
@@ -434,11 +434,11 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
     const int Q = A.Q, NP = A.NF * A.Q;
     auto group = [&](int g, T* xo, int& nq) {
         const int pp = min(4 * g + h, NP - 1);
-        const T* X = A.xi + int64_t(pp) * 3 * nc + c;
+        const T* X = A.xi + int64_t(pp) * 3 * ns + c;
         xo[0] = X[0];
-        xo[1] = X[nc];
-        xo[2] = X[2 * nc];
-        nq = A.cnq[int64_t(pp / Q) * nc + c];
+        xo[1] = X[ns];
+        xo[2] = X[2 * ns];
+        nq = A.cnq[int64_t(pp / Q) * ns + c];
     };
     auto point = [&](int p, T x, T y, T z) {
         T t[K];
@@ -497,9 +497,9 @@ __global__ __launch_bounds__(kBlock) void reconstruct_p4_fallback_kernel(ReconAr
     if (c >= A.nc) return;
     const uint8_t fl = A.flags[c];
     if (!(fl & 0x80)) return;
-    const int64_t nc = A.nc;
+    const int64_t nc = A.nc, ns = A.ns;
     for (int lf = 0; lf < A.NF; ++lf) {
-        const int nq = A.cnq[int64_t(lf) * nc + c];
+        const int nq = A.cnq[int64_t(lf) * ns + c];
         for (int q = 0; q < nq; ++q)
             for (int v = 0; v < 5; ++v)
                 A.fs[((int64_t(lf) * A.Q + q) * fs_cells_padded(nc) + c) * 5 + v] = T(A.U[v * nc + c]);

@@ -47,14 +47,25 @@ inline uint64_t recon_span_bytes(int64_t nc, int elem_bytes, int K, int NF) {
                               uint64_t(5) * uint64_t(elem_bytes) * uint64_t(fs_cells_padded(nc)));
 }
 constexpr uint64_t kMaxDescriptorBytes = 0xffffffffull;
+// Row stride of the per-cell mesh arrays ([row][stride]): the cell count
+// padded to whole 64-cell tiles, so that a wave's run of a row starts on a
+// cache line (an odd cell count would have it touch three 128-byte lines where
+// two hold it, and the streamed lines shared with the next wave be fetched
+// twice); the plain count where the padding would push a descriptor past its
+// limit.
+inline int64_t row_stride(int64_t nc, int K) {
+    const int64_t padded = fs_cells_padded(nc);
+    return uint64_t(std::max(K, 5)) * 8u * uint64_t(padded) <= kMaxDescriptorBytes ? padded : nc;
+}
 
 
-// Offsets (bytes) of every array inside one precision's device arena.
+// Offsets (bytes) of every array inside one precision's device arena (per-cell
+// arrays [row][ns], ns = Mesh::ns).
 struct Arena {
     size_t bytes = 0;
     size_t sten_c = 0, Bc = 0, ndir = 0, sten_d = 0, Bd = 0, O = 0, xi = 0, pmean = 0, c2f = 0;
-    // smoothness indicators: V^(2/3) / h^2 per cell, and the scaled moments of degree r+1 .. 2r-2
-    // (pmean holds those up to r), which fix the indicator matrix; P4 still reads the matrix O
+    // smoothness indicators: V^(2/3) / h^2 per cell and the scaled moments of degree 4 (P3); where
+    // reads_indicator_matrix, the matrix O
     size_t th = 0, mom = 0;
     size_t cnq = 0;  // [nfmax][nc] Gauss points of each of a cell's face slots (0: no face)
     size_t vol = 0, hdt = 0, fcell = 0, flf = 0, fnrm = 0, farea = 0, fw = 0, fdc = 0, fnq = 0;
@@ -67,14 +78,16 @@ struct Arena {
     void* dev = nullptr;  // caller-owned device pointer after upload
 };
 
-// Scaled moments mean(((x - c)/h)^e) of degree r+1 .. 2r-2 (P2: none, P3: the
-// 15 of degree 4), the ones the smoothness indicators need beside the basis
-// means; in the basis' graded-lex order, degree by degree.
+// Scaled moments mean(((x - c)/h)^e) of degree 4, beyond those the basis means
+// hold, that the smoothness indicators of P3 need (graded-lex order).
 constexpr int num_indicator_moments(int order) { return order == 3 ? 15 : 0; }
+// Whether the reconstruction reads the indicator matrix itself (si_opt).
+constexpr bool reads_indicator_matrix(int order, int elem_bytes) { return order == 4 || (order == 2 && elem_bytes == 4); }
 
 struct Mesh {
     // ---- input
     int64_t nv = 0, nc = 0;
+    int64_t ns = 0;  // row_stride of the device arrays
     std::vector<double> xyz;
     std::vector<uint8_t> type;
     std::vector<int64_t> cptr, cvtx;

@@ -32,6 +32,7 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kRedBlocks = 1024;  // fixed grid of the deterministic reductions
+constexpr int64_t kInfinityCache = int64_t(256) << 20;  // bytes of the memory-side cache
 
 // The dispatcher hands workgroups to the eight XCDs round robin (block b runs
 // on XCD b mod 8).  Renumbered this way, each XCD takes one contiguous range
@@ -86,6 +87,7 @@ template <class T>
 struct ReconArgs {
     const double* U;
     int64_t nc;
+    int64_t ns;  // row stride of the mesh arrays ([row][ns])
     const int32_t* sten_c;
     const T* Bc;
     int MC;
@@ -95,15 +97,16 @@ struct ReconArgs {
     const T* Bd;
     int ND;       // directional stencil slots per cell (cells with fewer pad with zero operators)
     int MD;       // padded directional stencil size
-    const T* O;    // P4: upper triangle of the indicator matrix
-    const T* th;   // V^(2/3) / h^2 per cell
-    const T* mom;  // P3: scaled moments of degree 4 [15][nc]
+    const T* O;    // upper triangle of the indicator matrix (reads_indicator_matrix)
+    const T* th;   // V^(2/3) / h^2 per cell: the linear block of O is th times the identity
+    const T* mom;  // P3: scaled moments of degree 4 [15][ns]
     const T* xi;     // face points in each cell's scaled frame [lf][q][3][nc]
     const T* pmean;  // cell means of the scaled monomials [K][nc]
     const uint8_t* cnq;  // Gauss points of each face slot [lf][nc] (0: no face)
     int Q, NF;
     const uint8_t* gate;
     T* fs;
+    bool fs_nt;  // store the point states non-temporally (make_recon_args)
     uint8_t* flags;
     float* label;
     T lam_c, eps, gm1;
@@ -124,7 +127,7 @@ struct ReconArgs {
     T gM2;
 };
 
-template <class T, bool LSQ>
+template <class T, bool LSQ, bool NT>
 __device__ void cell_gradient(const ReconArgs<T>& A, int64_t c, const double* ui);
 
 __device__ __forceinline__ int tri_index(int K, int k, int l) { return k * K - (k * (k - 1)) / 2 + (l - k); }
@@ -301,7 +304,7 @@ __device__ __forceinline__ void ghost(const BcT<T>& B, int tag, const T* in, con
 template <class T>
 struct GradArgs {
     const double* U;
-    int64_t nc;
+    int64_t nc, ns;
     const int32_t* c2f;
     int NF;
     const int32_t* fcell;
@@ -334,7 +337,7 @@ __global__ __launch_bounds__(kBlock) void gradients_kernel(GradArgs<T> A, PhysT<
     for (int g0 = 0; g0 < kMaxFaces; g0 += G) {
         int32_t f2[G], other[G];
 #pragma unroll
-        for (int i = 0; i < G; ++i) f2[i] = g0 + i < A.NF ? A.c2f[int64_t(g0 + i) * nc + c] : -1;
+        for (int i = 0; i < G; ++i) f2[i] = g0 + i < A.NF ? A.c2f[int64_t(g0 + i) * A.ns + c] : -1;
         // absent slots read face 0 and boundary sides cell 0, and are
         // skipped or replaced below: every load is unconditional (a load
         // under a lane condition would be a branch that waits for it)
@@ -349,7 +352,7 @@ __global__ __launch_bounds__(kBlock) void gradients_kernel(GradArgs<T> A, PhysT<
                 const int slot = g0 + i < A.NF ? g0 + i : 0;
                 sa[i] = T(0);
 #pragma unroll
-                for (int a = 0; a < 3; ++a) nr[i][a] = A.glsq[int64_t(3 * slot + a) * nc + c];
+                for (int a = 0; a < 3; ++a) nr[i][a] = A.glsq[int64_t(3 * slot + a) * A.ns + c];
             } else {
                 sa[i] = (side ? T(-0.5) : T(0.5)) * A.farea[f];
 #pragma unroll
@@ -422,7 +425,7 @@ __device__ __forceinline__ void ghost_dev(const ucns_bc* bc, int tag, const T* i
 // boundary slot's neighbour entry is its face's negative tag (the ghost state
 // enters), an absent slot's weights are zero.  The neighbours' states were
 // gathered by the cell's central stencil a moment earlier.
-template <class T, bool LSQ>
+template <class T, bool LSQ, bool NT>
 __device__ void cell_gradient(const ReconArgs<T>& A, int64_t c, const double* ui) {
     const int64_t nc = A.nc;
     // W of a state, as prim_W forms it
@@ -447,11 +450,12 @@ __device__ void cell_gradient(const ReconArgs<T>& A, int64_t c, const double* ui
     for (int lf = 0; lf < kMaxFaces; ++lf) {
         const bool have = lf < A.NF;
         const int64_t r = have ? lf : 0;
-        const int32_t j = A.nbr[r * nc + c];
+        const int32_t j = A.nbr[r * A.ns + c];
         jn[lf] = have ? j : -1;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const T x = (LSQ ? A.glsq : A.ggw)[(3 * r + a) * nc + c];
+            const T* px = (LSQ ? A.glsq : A.ggw) + (3 * r + a) * A.ns + c;
+            const T x = NT ? __builtin_nontemporal_load(px) : *px;
             w[lf][a] = have ? x : T(0);
         }
     }
@@ -470,7 +474,7 @@ __device__ void cell_gradient(const ReconArgs<T>& A, int64_t c, const double* ui
             // only read it for the least-squares sum)
             T gw[3];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) gw[a] = LSQ ? (lf < A.NF ? A.ggw[int64_t(3 * lf + a) * nc + c] : T(0)) : w[lf][a];
+            for (int a = 0; a < 3; ++a) gw[a] = LSQ ? (lf < A.NF ? A.ggw[int64_t(3 * lf + a) * A.ns + c] : T(0)) : w[lf][a];
             const T wn = sqrt(gw[0] * gw[0] + gw[1] * gw[1] + gw[2] * gw[2]);
             const T iw = wn > T(0) ? T(1) / wn : T(0);
             const T nb[3] = {gw[0] * iw, gw[1] * iw, gw[2] * iw};
@@ -675,7 +679,7 @@ __global__ __launch_bounds__(kBlock) void face_flux_kernel(FluxArgs<T> A, PhysT<
 template <class T>
 struct ResArgs {
     const T* ff;
-    int64_t nc;
+    int64_t nc, ns;
     const int32_t* c2f;
     int NF;
     const double* vol;
@@ -710,7 +714,7 @@ template <class T>
 __device__ __forceinline__ void face_sum(const ResArgs<T>& A, int64_t c, double acc[5]) {
     int32_t f2[kMaxFaces];
 #pragma unroll
-    for (int lf = 0; lf < kMaxFaces; ++lf) f2[lf] = lf < A.NF ? A.c2f[int64_t(lf) * A.nc + c] : -1;
+    for (int lf = 0; lf < kMaxFaces; ++lf) f2[lf] = lf < A.NF ? A.c2f[int64_t(lf) * A.ns + c] : -1;
     // absent slots load face 0 and are skipped below (a load under a lane
     // condition would be a branch that waits for it)
     T fl[kMaxFaces][5];
@@ -989,6 +993,7 @@ ReconArgs<T> make_recon_args(const Mesh& m, const Arena& ar, double gm1, const d
     ReconArgs<T> A;
     A.U = U;
     A.nc = m.nc;
+    A.ns = m.ns;
     A.sten_c = arena_ptr<int32_t>(ar, ar.sten_c);
     A.Bc = arena_ptr<T>(ar, ar.Bc);
     A.MC = m.mc_pad;
@@ -1016,6 +1021,11 @@ ReconArgs<T> make_recon_args(const Mesh& m, const Arena& ar, double gm1, const d
     // the arena's one scratch region (written by the P4 reconstruction call)
     A.ustage = ar.ustage ? reinterpret_cast<double*>(static_cast<unsigned char*>(ar.dev) + ar.ustage) : nullptr;
     A.fs = static_cast<T*>(fs);
+    // point states that fit the Infinity Cache are still there when the flux
+    // kernel reads them (64^3 gated FP32 step, 126 MB: 573 us, 582 us with
+    // non-temporal stores); larger ones only push other data out (284,000
+    // mixed FP64 cells, 273 MB: 441 us, 432 us non-temporally)
+    A.fs_nt = int64_t(sizeof(T)) * 5 * m.nfmax * m.qmax * fs_cells_padded(m.nc) > kInfinityCache;
     A.flags = flags;
     A.label = label;
     A.lam_c = T(m.lambda_c);
@@ -1033,7 +1043,7 @@ ReconArgs<T> make_recon_args(const Mesh& m, const Arena& ar, double gm1, const d
 template <class T>
 void launch_gradients(const Mesh& m, const Arena& ar, const ucns_phys* phys, const ucns_bc* bc, const double* U,
                       void* gradW, hipStream_t st) {
-    GradArgs<T> A{U, m.nc, arena_ptr<int32_t>(ar, ar.c2f), m.nfmax, arena_ptr<int32_t>(ar, ar.fcell),
+    GradArgs<T> A{U, m.nc, m.ns, arena_ptr<int32_t>(ar, ar.c2f), m.nfmax, arena_ptr<int32_t>(ar, ar.fcell),
                   arena_ptr<T>(ar, ar.fnrm), arena_ptr<T>(ar, ar.farea), arena_ptr<double>(ar, ar.vol),
                   arena_ptr<T>(ar, ar.glsq), static_cast<T*>(gradW)};
     if (phys->grad == UCNS_GRAD_LSQ)
@@ -1044,38 +1054,68 @@ void launch_gradients(const Mesh& m, const Arena& ar, const ucns_phys* phys, con
                            make_phys<T>(phys), make_bc<T>(bc));
 }
 
-template <class T, int K>
-int launch_recon_k(const ReconArgs<T>& A, hipStream_t st, bool grad_lsq = false) {
-    if (A.Q > face_qmax<K>()) return UCNS_EINVAL;
-    if (recon_span_bytes(A.nc, int(sizeof(T)), K, A.NF) > kMaxDescriptorBytes) return UCNS_EINVAL;
+// Whether a call's operator streams are read non-temporally.  Streams that
+// the Infinity Cache (256 MB) cannot hold from one call to the next evict
+// themselves, and marked they run faster (6.6 against 5.8 TB/s for a pure
+// stream; 64^3 gated FP32 step 610 -> 573 us, 375,000 shocked tets 203 -> 196
+// us); of streams that fit, a marked read gives up the cached copy.  Measured
+// around the limit (plain / marked): P2 FP32 at 178 MB 75 / 91 us, 261 MB
+// 101 / 96 us; gated 160 MB 77 / 80 us, 250 MB 120 / 114 us; P2 FP64 213 MB
+// 75 / 74 us, 287 MB 135 / 125 us; P3 FP64 248 MB 104 / 106 us, 340 MB 115 /
+// 111 us; P3 FP32 235 MB 75 / 81 us, 305 MB 141 / 137 us.
+template <class T>
+bool nt_streams(const ReconArgs<T>& A, int K) {
+    const bool gate = A.mlp || A.gate;
+    const int64_t t = sizeof(T);
+    const int64_t central = t * K * A.MC + 4 * A.MC, dir = gate ? 0 : int64_t(A.ND) * A.MD * (3 * t + 4);
+    const int64_t slots = A.NF * ((gate || A.gradW ? 4 : 0) + 3 * t * ((A.mlp ? 1 : 0) + (A.gradW ? 1 : 0)));
+    return A.ns * (central + dir + t * 3 * A.NF * A.Q + slots) > kInfinityCache - (int64_t(6) << 20);
+}
+
+template <class T, int K, bool NT>
+int launch_recon_main(const ReconArgs<T>& A, hipStream_t st, bool grad_lsq) {
     const dim3 grid(grid_for(A.nc)), block(kBlock);
+    const bool gate = A.mlp || A.gate;
     if (A.gradW) {
         // the fused gradients (grad_lsq: least squares, else Green-Gauss): P2
         // only (the P3 kernels have no scalar registers to spare for the
         // extra arguments)
         if constexpr (K == 9) {
             if (A.label) return UCNS_EINVAL;
-            const bool gate = A.mlp || A.gate;
             if (grad_lsq && gate)
-                hipLaunchKernelGGL((reconstruct_kernel<T, K, false, true, 2>), grid, block, 0, st, A);
+                hipLaunchKernelGGL((reconstruct_kernel<T, K, false, true, 2, NT>), grid, block, 0, st, A);
             else if (grad_lsq)
-                hipLaunchKernelGGL((reconstruct_kernel<T, K, false, false, 2>), grid, block, 0, st, A);
+                hipLaunchKernelGGL((reconstruct_kernel<T, K, false, false, 2, NT>), grid, block, 0, st, A);
             else if (gate)
-                hipLaunchKernelGGL((reconstruct_kernel<T, K, false, true, 1>), grid, block, 0, st, A);
+                hipLaunchKernelGGL((reconstruct_kernel<T, K, false, true, 1, NT>), grid, block, 0, st, A);
             else
-                hipLaunchKernelGGL((reconstruct_kernel<T, K, false, false, 1>), grid, block, 0, st, A);
+                hipLaunchKernelGGL((reconstruct_kernel<T, K, false, false, 1, NT>), grid, block, 0, st, A);
         } else {
             return UCNS_EINVAL;
         }
-    } else if (A.mlp || A.gate) {
-        hipLaunchKernelGGL((reconstruct_kernel<T, K, false, true>), grid, block, 0, st, A);
+    } else if (gate) {
+        hipLaunchKernelGGL((reconstruct_kernel<T, K, false, true, 0, NT>), grid, block, 0, st, A);
     } else {
-        if (A.label)
-            hipLaunchKernelGGL((reconstruct_kernel<T, K, true, false>), grid, block, 0, st, A);
-        else
-            hipLaunchKernelGGL((reconstruct_kernel<T, K, false, false>), grid, block, 0, st, A);
+        if constexpr (!NT) {
+            if (A.label) {
+                hipLaunchKernelGGL((reconstruct_kernel<T, K, true, false, 0, false>), grid, block, 0, st, A);
+                return UCNS_OK;
+            }
+        }
+        hipLaunchKernelGGL((reconstruct_kernel<T, K, false, false, 0, NT>), grid, block, 0, st, A);
     }
-    hipLaunchKernelGGL((reconstruct_fallback_kernel<T, K>), grid, block, 0, st, A);
+    return UCNS_OK;
+}
+
+template <class T, int K>
+int launch_recon_k(const ReconArgs<T>& A, hipStream_t st, bool grad_lsq = false) {
+    if (A.Q > face_qmax<K>()) return UCNS_EINVAL;
+    if (recon_span_bytes(A.nc, int(sizeof(T)), K, A.NF) > kMaxDescriptorBytes) return UCNS_EINVAL;
+    // (the labelled variant serves the gate's data collection only)
+    const int rc = nt_streams(A, K) && !A.label ? launch_recon_main<T, K, true>(A, st, grad_lsq)
+                                    : launch_recon_main<T, K, false>(A, st, grad_lsq);
+    if (rc != UCNS_OK) return rc;
+    hipLaunchKernelGGL((reconstruct_fallback_kernel<T, K>), dim3(grid_for(A.nc)), dim3(kBlock), 0, st, A);
     return UCNS_OK;
 }
 
@@ -1447,7 +1487,7 @@ int launch_residual(const ucns_mesh* mesh, const void* face_flux, int precision,
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     auto go = [&](auto zero) {
         using T = decltype(zero);
-        ResArgs<T> A{static_cast<const T*>(face_flux), m.nc, arena_ptr<int32_t>(ar, ar.c2f), m.nfmax,
+        ResArgs<T> A{static_cast<const T*>(face_flux), m.nc, m.ns, arena_ptr<int32_t>(ar, ar.c2f), m.nfmax,
                      arena_ptr<double>(ar, ar.vol), R, U0, U, dt_dev, stage >= 0 ? Ac[stage] : 0.0,
                      stage >= 0 ? Bc_[stage] : 0.0, stage};
         if (stage >= 0)
@@ -1491,7 +1531,7 @@ int ucns_residual_ssp54_stage(const ucns_mesh* mesh, const void* face_flux, int 
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     auto go = [&](auto zero) {
         using T = decltype(zero);
-        ResArgs<T> A{static_cast<const T*>(face_flux), m.nc, arena_ptr<int32_t>(ar, ar.c2f), m.nfmax,
+        ResArgs<T> A{static_cast<const T*>(face_flux), m.nc, m.ns, arena_ptr<int32_t>(ar, ar.c2f), m.nfmax,
                      arena_ptr<double>(ar, ar.vol), nullptr, nullptr, U, dt_dev, 0.0, 0.0, stage};
         hipLaunchKernelGGL(residual_ssp54_kernel<T>, dim3(grid_for(m.nc)), dim3(kBlock), 0, st, A, W);
     };
@@ -1528,7 +1568,7 @@ int launch_rk_final(const ucns_mesh* mesh, const ucns_phys* phys, const void* fa
     const unsigned nb = grid_for(m.nc);
     auto go = [&](auto zero) {
         using T = decltype(zero);
-        ResArgs<T> A{static_cast<const T*>(face_flux), m.nc, arena_ptr<int32_t>(ar, ar.c2f), m.nfmax,
+        ResArgs<T> A{static_cast<const T*>(face_flux), m.nc, m.ns, arena_ptr<int32_t>(ar, ar.c2f), m.nfmax,
                      arena_ptr<double>(ar, ar.vol), nullptr, U0, U, dt_dev, 1.0 / 3.0, 2.0 / 3.0, 2,
                      arena_ptr<double>(ar, ar.hdt), make_phys<double>(phys), scratch};
         hipLaunchKernelGGL((residual_kernel<T, true, true>), dim3(nb), dim3(kBlock), 0, st, A);
