@@ -407,7 +407,7 @@ int ucns_gate_mask(const float* params, const float* features, int64_t n, uint8_
  * grads receives the batch gradient (parameter layout), adam_state holds m
  * then v (2 x UCNS_MLP_NPARAM floats), loss_dev the mean loss.  Only the
  * slots W1 .. b3 are trained; mu, isig and theta are the caller's.  The
- * batch is split over up to 64 one-wave blocks whose gradient partials are
+ * batch is split over up to 64 blocks whose gradient partials are
  * summed in block order, so the result depends on n and the data only.  The
  * partials live in a fixed 1.3 MiB device array per GPU: steps on one GPU
  * must be ordered (one stream); overlapping steps race. */

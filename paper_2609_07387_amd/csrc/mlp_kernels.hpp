@@ -315,8 +315,8 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const float* __restric
 
 // ----------------------------------------------------------------- training
 //
-// The batch is cut into chunks of 64 samples (lane = sample); block b (one
-// wave) takes chunks b, b + nblk, ... and writes its gradient partial:
+// The batch is cut into chunks of 64 samples; block b (four waves) takes chunks
+// b, b + nblk, ... and writes its gradient partial:
 //   x = bf16((f - mu) isig); H1 = relu(x W1 + b1); H2 = relu(bf16(H1) W2 + b2)
 //   z = H2 . w3 + b3; loss = mean_w BCE(z, y); dz = w (sigmoid(z) - y) / B
 //   dH2 = dz w3 [H2 > 0]; dW2 = bf16(H1)^T bf16(dH2); dw3 = H2^T dz
@@ -324,243 +324,287 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const float* __restric
 // mlp_adam_kernel then sums the partials in block order (the result depends
 // on n only, not on scheduling) and applies Adam (FP32 master weights) on the
 // trainable slots.
+//
+// A step is one short chain of dependent work, bound by latency.  Wave w takes
+// the chunk's samples 16 w .. 16 w + 15 through both layers and back (its rows
+// of H1, H2, dH2 and dH1 stay in the wave: no barrier), then, after one block
+// barrier, the gradient tiles of hidden units 16 w .. 16 w + 15, which sum over
+// all 64 samples.  The weights are staged by all 256 threads with every load
+// issued at once.  One wave per chunk doing all of it took 44.8 us of a 50.4 us
+// step at 1,024 rows (staging alone 144 dependent rounds); the step now takes 13.8 us.
 namespace mlp {
 constexpr int kTrainMaxBlocks = 64;
 constexpr int kTrainStride = 5376;  // floats per partial row: kNParam slots, then the loss
+constexpr int kTrainWaves = 4;      // one per 16 samples of a chunk
 }  // namespace mlp
 struct TrainLds {
-    MlpWeights S;
-    uint16_t W2r[64 * mlp::kHS];   // [k_in][n_out] (row-major W2) for dH1
-    uint16_t Xs[64 * mlp::kXS];    // [r][k]
-    uint16_t Xt[16 * mlp::kHS];    // [k][r]
-    uint16_t Hs[64 * mlp::kHS];    // bf16(H1) [r][i]
-    uint16_t H1t[64 * mlp::kHS];   // [i][r]; later dH1 [i][r]
-    uint16_t dH2s[64 * mlp::kHS];  // [r][n]
-    uint16_t dH2t[64 * mlp::kHS];  // [n][r]
-    float z[64], dz[64];
-    float red[64];
+    alignas(16) uint16_t W1t[64 * mlp::kXS];   // [n][k], k < 16
+    alignas(16) uint16_t W2t[64 * mlp::kHS];   // [n_out][k_in]
+    alignas(16) uint16_t W2r[64 * mlp::kHS];   // [k_in][n_out] (row-major W2) for dH1
+    alignas(16) uint16_t Xs[64 * mlp::kXS];    // [r][k]
+    alignas(16) uint16_t Xt[16 * mlp::kHS];    // [k][r]
+    alignas(16) uint16_t Hs[64 * mlp::kHS];    // bf16(H1) [r][i]
+    alignas(16) uint16_t H1t[64 * mlp::kHS];   // bf16(H1) [i][r]
+    alignas(16) uint16_t D1t[64 * mlp::kHS];   // bf16(dH1) [i][r]
+    alignas(16) uint16_t dH2s[64 * mlp::kHS];  // [r][n]
+    alignas(16) uint16_t dH2t[64 * mlp::kHS];  // [n][r]
+    float b1[64], b2[64], w3[64], mu[16], isig[16];
+    float red[mlp::kTrainWaves][3][64];  // the waves' column sums: db1, db2, dw3
+    float red2[mlp::kTrainWaves][2];     // db3, loss
 };
 
-__global__ __launch_bounds__(64) void mlp_train_kernel(const float* __restrict__ P, float* __restrict__ part,
-                                                       const float* __restrict__ feat, const float* __restrict__ lab,
-                                                       int64_t n, float pos_w) {
+// four bf16 values packed for one 8-byte LDS write
+__device__ __forceinline__ uint2 pack4(const uint16_t* h) {
+    return make_uint2(uint32_t(h[0]) | (uint32_t(h[1]) << 16), uint32_t(h[2]) | (uint32_t(h[3]) << 16));
+}
+
+__global__ __launch_bounds__(64 * mlp::kTrainWaves) void mlp_train_kernel(const float* __restrict__ P,
+                                                                          float* __restrict__ part,
+                                                                          const float* __restrict__ feat,
+                                                                          const float* __restrict__ lab, int64_t n,
+                                                                          float pos_w) {
     __shared__ TrainLds L;
-    const int lane = threadIdx.x, g = lane >> 4, r = lane & 15;
-    mlp_stage(P, L.S, lane, 64);
-    for (int i = lane; i < 64 * 64; i += 64) {
-        const int k = i >> 6, nn = i & 63;
-        L.W2r[k * mlp::kHS + nn] = f2bf(P[mlp::kOffW2 + k * 64 + nn]);
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, g = lane >> 4, r = lane & 15;
+    const int64_t nch = (n + 63) / 64;
+    const ucns_f32x4 zero4{0.f, 0.f, 0.f, 0.f};
+    // every global load of the stage first: weights, vectors, the chunk's features
+    auto load_features = [&](int64_t ch, float* f) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const int64_t i = ch * 768 + tid + 256 * q;  // rows of 12 features are contiguous
+            f[q] = i < n * 12 ? feat[i] : 0.f;
+        }
+    };
+    float fx[3];
+    load_features(blockIdx.x, fx);
+    {
+        float v2[16], v1[4];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v2[q] = P[mlp::kOffW2 + tid + 256 * q];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v1[q] = P[mlp::kOffW1 + tid + 256 * q];
+        const float vb = w == 0 ? P[mlp::kOffB1 + lane] : w == 1 ? P[mlp::kOffB2 + lane] : w == 2 ? P[mlp::kOffW3 + lane]
+                         : lane < 32 ? P[mlp::kOffMu + lane] : 0.f;  // mu and isig are adjacent
+        const int k0 = tid >> 6, nn = tid & 63;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const uint16_t h = f2bf(v2[q]);
+            L.W2t[nn * mlp::kHS + k0 + 4 * q] = h;
+            L.W2r[(k0 + 4 * q) * mlp::kHS + nn] = h;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) L.W1t[nn * mlp::kXS + k0 + 4 * q] = f2bf(v1[q]);
+        if (w == 0)
+            L.b1[lane] = vb;
+        else if (w == 1)
+            L.b2[lane] = vb;
+        else if (w == 2)
+            L.w3[lane] = vb;
+        else if (lane < 16)
+            L.mu[lane] = vb;
+        else if (lane < 32)
+            L.isig[lane - 16] = vb;
+        // inputs 12 .. 15 are padding
+        const int pr = tid >> 2, pk = 12 + (tid & 3);
+        L.Xs[pr * mlp::kXS + pk] = 0;
+        L.Xt[pk * mlp::kHS + pr] = 0;
     }
+    const float b3 = P[mlp::kOffB3];
     __syncthreads();
-    const MlpWeights& S = L.S;
-    // gradient accumulators: dW1 tile (k, n) for nt; dW2 tiles (it, nt); per-lane column sums
-    ucns_f32x4 gW1[4], gW2[4][4];
+    // gradient accumulators: tile rows are hidden units 16 w .. (dW2) and
+    // inputs (dW1); the column sums are this lane's share of its wave's rows
+    ucns_f32x4 gW1 = zero4, gW2[4];
+    float ab1[4], ab2[4], aw3[4], gb3 = 0.f, lsum = 0.f;
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
-        gW1[a] = ucns_f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int b = 0; b < 4; ++b) gW2[a][b] = ucns_f32x4{0.f, 0.f, 0.f, 0.f};
+        gW2[a] = zero4;
+        ab1[a] = ab2[a] = aw3[a] = 0.f;
     }
-    float gb1 = 0.f, gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, lsum = 0.f;  // lane = column index
     const float inv_b = 1.f / float(n);
-    const int64_t nch = (n + 63) / 64;
+    const int row0 = 16 * w + 4 * g;  // this lane's output rows (samples) row0 .. row0 + 3
     for (int64_t ch = blockIdx.x; ch < nch; ch += gridDim.x) {
-        const int64_t i = ch * 64 + lane;
-        const bool valid = i < n;
-        // ---- inputs
+        // ---- inputs (the next chunk's features load meanwhile) and labels
+        float y[4], wcls[4];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const float x = (k < 12 && valid) ? (feat[i * 12 + k] - S.mu[k]) * S.isig[k] : 0.f;
-            const uint16_t xb = f2bf(x);
-            L.Xs[lane * mlp::kXS + k] = xb;
-            L.Xt[k * mlp::kHS + lane] = xb;
-        }
-        const float y = valid ? lab[i] : 0.f;
-        const float wcls = valid ? (y > 0.5f ? pos_w : 1.f) : 0.f;
-        __builtin_amdgcn_wave_barrier();
-        // ---- layer 1
-        ucns_bf16x8 ax[4];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) ax[mt] = g < 2 ? lds8(&L.Xs[(16 * mt + r) * mlp::kXS + 8 * g]) : zero8();
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const ucns_bf16x8 bw = g < 2 ? lds8(&S.W1t[(16 * nt + r) * mlp::kXS + 8 * g]) : zero8();
-            const int nn = 16 * nt + r;
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                const ucns_f32x4 acc = mfma16(ax[mt], bw, ucns_f32x4{0.f, 0.f, 0.f, 0.f});
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint16_t hb = f2bf(fmaxf(acc[j] + S.b1[nn], 0.f));
-                    const int row = 16 * mt + 4 * g + j;
-                    L.Hs[row * mlp::kHS + nn] = hb;
-                    L.H1t[nn * mlp::kHS + row] = hb;
-                }
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        // ---- layer 2, pass A: logits
-        float part[4][4];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) part[mt][j] = 0.f;
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const ucns_bf16x8 b0 = lds8(&S.W2t[(16 * nt + r) * mlp::kHS + 8 * g]);
-            const ucns_bf16x8 b1 = lds8(&S.W2t[(16 * nt + r) * mlp::kHS + 32 + 8 * g]);
-            const int nn = 16 * nt + r;
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                ucns_f32x4 acc = mfma16(lds8(&L.Hs[(16 * mt + r) * mlp::kHS + 8 * g]), b0, ucns_f32x4{0.f, 0.f, 0.f, 0.f});
-                acc = mfma16(lds8(&L.Hs[(16 * mt + r) * mlp::kHS + 32 + 8 * g]), b1, acc);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) part[mt][j] += fmaxf(acc[j] + S.b2[nn], 0.f) * S.w3[nn];
-            }
+        for (int j = 0; j < 4; ++j) {
+            const int64_t i = ch * 64 + row0 + j;
+            y[j] = i < n ? lab[i] : 0.f;
+            wcls[j] = i < n ? (y[j] > 0.5f ? pos_w : 1.f) : 0.f;
         }
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                float v = part[mt][j];
-                v += __shfl_xor(v, 1, 16);
-                v += __shfl_xor(v, 2, 16);
-                v += __shfl_xor(v, 4, 16);
-                v += __shfl_xor(v, 8, 16);
-                if (r == 0) L.z[16 * mt + 4 * g + j] = v + S.b3;
-            }
-        __builtin_amdgcn_wave_barrier();
+        for (int q = 0; q < 3; ++q) {
+            const int e = tid + 256 * q, row = e / 12, k = e - 12 * row;
+            const uint16_t xb = ch * 64 + row < n ? f2bf((fx[q] - L.mu[k]) * L.isig[k]) : uint16_t(0);
+            L.Xs[row * mlp::kXS + k] = xb;
+            L.Xt[k * mlp::kHS + row] = xb;
+        }
+        if (ch + gridDim.x < nch) load_features(ch + gridDim.x, fx);
+        __syncthreads();
+        // ---- layer 1: the wave's 16 samples
         {
-            const float z = L.z[lane];
-            const float s = 1.f / (1.f + __expf(-z));
-            const float d = wcls * (s - y) * inv_b;
-            L.dz[lane] = d;
-            // BCE with logits: log(1 + e^-|z|) + max(z, 0) - z y
-            lsum += wcls * (log1pf(__expf(-fabsf(z))) + fmaxf(z, 0.f) - z * y);
-            gb3 += d;
-        }
-        __builtin_amdgcn_wave_barrier();
-        // ---- layer 2, pass B: dH2, dw3, db2 (recomputing H2 from the same products)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const ucns_bf16x8 b0 = lds8(&S.W2t[(16 * nt + r) * mlp::kHS + 8 * g]);
-            const ucns_bf16x8 b1 = lds8(&S.W2t[(16 * nt + r) * mlp::kHS + 32 + 8 * g]);
-            const int nn = 16 * nt + r;
-            float cw3 = 0.f, cb2 = 0.f;
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                ucns_f32x4 acc = mfma16(lds8(&L.Hs[(16 * mt + r) * mlp::kHS + 8 * g]), b0, ucns_f32x4{0.f, 0.f, 0.f, 0.f});
-                acc = mfma16(lds8(&L.Hs[(16 * mt + r) * mlp::kHS + 32 + 8 * g]), b1, acc);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int row = 16 * mt + 4 * g + j;
-                    const float h2p = acc[j] + S.b2[nn];
-                    const float dzr = L.dz[row];
-                    const float dh2 = h2p > 0.f ? dzr * S.w3[nn] : 0.f;
-                    cw3 += fmaxf(h2p, 0.f) * dzr;
-                    cb2 += dh2;
-                    const uint16_t db = f2bf(dh2);
-                    L.dH2s[row * mlp::kHS + nn] = db;
-                    L.dH2t[nn * mlp::kHS + row] = db;
-                }
-            }
-            // sum the column's partials over the 4 lane groups
-            cw3 += __shfl_xor(cw3, 16);
-            cw3 += __shfl_xor(cw3, 32);
-            cb2 += __shfl_xor(cb2, 16);
-            cb2 += __shfl_xor(cb2, 32);
-            if (g == nt) {  // lane 16 nt + r keeps column nn = lane
-                gw3 += cw3;
-                gb2 += cb2;
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        // ---- dW2[i][n] += sum_r H1[r][i] dH2[r][n]   (K = 64 samples = 2 steps)
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const ucns_bf16x8 a0 = lds8(&L.H1t[(16 * it + r) * mlp::kHS + 8 * g]);
-            const ucns_bf16x8 a1 = lds8(&L.H1t[(16 * it + r) * mlp::kHS + 32 + 8 * g]);
+            const ucns_bf16x8 ax = g < 2 ? lds8(&L.Xs[(16 * w + r) * mlp::kXS + 8 * g]) : zero8();
 #pragma unroll
             for (int nt = 0; nt < 4; ++nt) {
-                gW2[it][nt] = mfma16(a0, lds8(&L.dH2t[(16 * nt + r) * mlp::kHS + 8 * g]), gW2[it][nt]);
-                gW2[it][nt] = mfma16(a1, lds8(&L.dH2t[(16 * nt + r) * mlp::kHS + 32 + 8 * g]), gW2[it][nt]);
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        // ---- dH1[r][i] = sum_n dH2[r][n] W2[i][n] [H1 > 0]; written as [i][r] over H1t
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const ucns_bf16x8 b0 = lds8(&L.W2r[(16 * it + r) * mlp::kHS + 8 * g]);
-            const ucns_bf16x8 b1 = lds8(&L.W2r[(16 * it + r) * mlp::kHS + 32 + 8 * g]);
-            const int ii = 16 * it + r;
-            float cb1 = 0.f;
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                ucns_f32x4 acc = mfma16(lds8(&L.dH2s[(16 * mt + r) * mlp::kHS + 8 * g]), b0, ucns_f32x4{0.f, 0.f, 0.f, 0.f});
-                acc = mfma16(lds8(&L.dH2s[(16 * mt + r) * mlp::kHS + 32 + 8 * g]), b1, acc);
+                const int nn = 16 * nt + r;
+                const ucns_bf16x8 bw = g < 2 ? lds8(&L.W1t[nn * mlp::kXS + 8 * g]) : zero8();
+                const ucns_f32x4 acc = mfma16(ax, bw, zero4);
+                uint16_t hb[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const int row = 16 * mt + 4 * g + j;
-                    const float dh1 = (L.Hs[row * mlp::kHS + ii] & 0x7FFF) != 0 ? acc[j] : 0.f;
-                    cb1 += dh1;
-                    L.H1t[ii * mlp::kHS + row] = f2bf(dh1);
+                    hb[j] = f2bf(fmaxf(acc[j] + L.b1[nn], 0.f));
+                    L.Hs[(row0 + j) * mlp::kHS + nn] = hb[j];
+                }
+                *reinterpret_cast<uint2*>(&L.H1t[nn * mlp::kHS + row0]) = pack4(hb);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        // ---- layer 2: pre-activations stay in registers; logits
+        float h2[4][4], z[4] = {0.f, 0.f, 0.f, 0.f};
+        {
+            const ucns_bf16x8 a0 = lds8(&L.Hs[(16 * w + r) * mlp::kHS + 8 * g]);
+            const ucns_bf16x8 a1 = lds8(&L.Hs[(16 * w + r) * mlp::kHS + 32 + 8 * g]);
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) {
+                const int nn = 16 * nt + r;
+                ucns_f32x4 acc = mfma16(a0, lds8(&L.W2t[nn * mlp::kHS + 8 * g]), zero4);
+                acc = mfma16(a1, lds8(&L.W2t[nn * mlp::kHS + 32 + 8 * g]), acc);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    h2[nt][j] = acc[j] + L.b2[nn];
+                    z[j] += fmaxf(h2[nt][j], 0.f) * L.w3[nn];
                 }
             }
-            cb1 += __shfl_xor(cb1, 16);
-            cb1 += __shfl_xor(cb1, 32);
-            if (g == it) gb1 += cb1;
         }
-        __builtin_amdgcn_wave_barrier();
-        // ---- dW1[k][i] += sum_r x[r][k] dH1[r][i]  (M = 16 inputs)
-        {
-            const ucns_bf16x8 a0 = lds8(&L.Xt[r * mlp::kHS + 8 * g]);
-            const ucns_bf16x8 a1 = lds8(&L.Xt[r * mlp::kHS + 32 + 8 * g]);
+        float d[4];
 #pragma unroll
-            for (int it = 0; it < 4; ++it) {
-                gW1[it] = mfma16(a0, lds8(&L.H1t[(16 * it + r) * mlp::kHS + 8 * g]), gW1[it]);
-                gW1[it] = mfma16(a1, lds8(&L.H1t[(16 * it + r) * mlp::kHS + 32 + 8 * g]), gW1[it]);
+        for (int j = 0; j < 4; ++j) {
+            z[j] += __shfl_xor(z[j], 1, 16);
+            z[j] += __shfl_xor(z[j], 2, 16);
+            z[j] += __shfl_xor(z[j], 4, 16);
+            z[j] += __shfl_xor(z[j], 8, 16);
+            z[j] += b3;
+            const float sg = 1.f / (1.f + __expf(-z[j]));
+            d[j] = wcls[j] * (sg - y[j]) * inv_b;
+            if (r == 0) {
+                // BCE with logits: log(1 + e^-|z|) + max(z, 0) - z y
+                lsum += wcls[j] * (log1pf(__expf(-fabsf(z[j]))) + fmaxf(z[j], 0.f) - z[j] * y[j]);
+                gb3 += d[j];
             }
         }
+        // ---- dH2, dw3, db2
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            const int nn = 16 * nt + r;
+            uint16_t db[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float dh2 = h2[nt][j] > 0.f ? d[j] * L.w3[nn] : 0.f;
+                aw3[nt] += fmaxf(h2[nt][j], 0.f) * d[j];
+                ab2[nt] += dh2;
+                db[j] = f2bf(dh2);
+                L.dH2s[(row0 + j) * mlp::kHS + nn] = db[j];
+            }
+            *reinterpret_cast<uint2*>(&L.dH2t[nn * mlp::kHS + row0]) = pack4(db);
+        }
         __builtin_amdgcn_wave_barrier();
+        // ---- dH1[r][i] = sum_n dH2[r][n] W2[i][n] [H1 > 0]
+        {
+            const ucns_bf16x8 a0 = lds8(&L.dH2s[(16 * w + r) * mlp::kHS + 8 * g]);
+            const ucns_bf16x8 a1 = lds8(&L.dH2s[(16 * w + r) * mlp::kHS + 32 + 8 * g]);
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const int ii = 16 * it + r;
+                ucns_f32x4 acc = mfma16(a0, lds8(&L.W2r[ii * mlp::kHS + 8 * g]), zero4);
+                acc = mfma16(a1, lds8(&L.W2r[ii * mlp::kHS + 32 + 8 * g]), acc);
+                uint16_t db[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float dh1 = (L.Hs[(row0 + j) * mlp::kHS + ii] & 0x7FFF) != 0 ? acc[j] : 0.f;
+                    ab1[it] += dh1;
+                    db[j] = f2bf(dh1);
+                }
+                *reinterpret_cast<uint2*>(&L.D1t[ii * mlp::kHS + row0]) = pack4(db);
+            }
+        }
+        __syncthreads();
+        // ---- dW2[i][n] += sum_r H1[r][i] dH2[r][n] for i = 16 w ..; dW1[k][i] += sum_r x[r][k] dH1[r][i]
+        {
+            const ucns_bf16x8 a0 = lds8(&L.H1t[(16 * w + r) * mlp::kHS + 8 * g]);
+            const ucns_bf16x8 a1 = lds8(&L.H1t[(16 * w + r) * mlp::kHS + 32 + 8 * g]);
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) {
+                gW2[nt] = mfma16(a0, lds8(&L.dH2t[(16 * nt + r) * mlp::kHS + 8 * g]), gW2[nt]);
+                gW2[nt] = mfma16(a1, lds8(&L.dH2t[(16 * nt + r) * mlp::kHS + 32 + 8 * g]), gW2[nt]);
+            }
+            gW1 = mfma16(lds8(&L.Xt[r * mlp::kHS + 8 * g]), lds8(&L.D1t[(16 * w + r) * mlp::kHS + 8 * g]), gW1);
+            gW1 = mfma16(lds8(&L.Xt[r * mlp::kHS + 32 + 8 * g]), lds8(&L.D1t[(16 * w + r) * mlp::kHS + 32 + 8 * g]), gW1);
+        }
+        __syncthreads();  // the next chunk overwrites what the other waves read here
     }
     // ---- this block's partial (parameter layout; every trainable slot written)
     float* G = part + int64_t(blockIdx.x) * mlp::kTrainStride;
 #pragma unroll
-    for (int it = 0; it < 4; ++it)
+    for (int j = 0; j < 4; ++j) {
+        const int k = 4 * g + j;  // input row of W1 (rows 12..15 are padding)
+        G[mlp::kOffW1 + k * 64 + 16 * w + r] = k < 12 ? gW1[j] : 0.f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int k = 4 * g + j;  // input row of W1 (rows 12..15 are padding)
-            G[mlp::kOffW1 + k * 64 + 16 * it + r] = k < 12 ? gW1[it][j] : 0.f;
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) G[mlp::kOffW2 + (16 * it + 4 * g + j) * 64 + 16 * nt + r] = gW2[it][nt][j];
-        }
-    G[mlp::kOffB1 + lane] = gb1;
-    G[mlp::kOffB2 + lane] = gb2;
-    G[mlp::kOffW3 + lane] = gw3;
-    // wave sums of gb3 (per-sample dz) and the loss
-    float s3 = gb3, sl = lsum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        s3 += __shfl_xor(s3, o);
-        sl += __shfl_xor(sl, o);
+        for (int nt = 0; nt < 4; ++nt) G[mlp::kOffW2 + (16 * w + 4 * g + j) * 64 + 16 * nt + r] = gW2[nt][j];
     }
+    // column sums over the wave's rows (the four lane groups), then over the
+    // waves; db3 and the loss over the lanes r = 0
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        float s[3] = {ab1[nt], ab2[nt], aw3[nt]};
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            s[q] += __shfl_xor(s[q], 16);
+            s[q] += __shfl_xor(s[q], 32);
+            if (g == 0) L.red[w][q][16 * nt + r] = s[q];
+        }
+    }
+    gb3 += __shfl_xor(gb3, 16);
+    gb3 += __shfl_xor(gb3, 32);
+    lsum += __shfl_xor(lsum, 16);
+    lsum += __shfl_xor(lsum, 32);
     if (lane == 0) {
-        G[mlp::kOffB3] = s3;
-        G[mlp::kNParam] = sl;
+        L.red2[w][0] = gb3;
+        L.red2[w][1] = lsum;
+    }
+    __syncthreads();
+    if (w < 3) {
+        const int off = w == 0 ? mlp::kOffB1 : w == 1 ? mlp::kOffB2 : mlp::kOffW3;
+        G[off + lane] = (L.red[0][w][lane] + L.red[1][w][lane]) + (L.red[2][w][lane] + L.red[3][w][lane]);
+    } else if (lane < 2) {
+        G[lane == 0 ? mlp::kOffB3 : mlp::kNParam] =
+            (L.red2[0][lane] + L.red2[1][lane]) + (L.red2[2][lane] + L.red2[3][lane]);
     }
 }
 
+// sum of slot i over the partials in block order, eight loads in flight
+__device__ __forceinline__ float train_sum(const float* __restrict__ part, int nblk, int i) {
+    float s = 0.f;
+    int b = 0;
+    for (; b + 8 <= nblk; b += 8) {
+        float x[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[q] = part[int64_t(b + q) * mlp::kTrainStride + i];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s += x[q];
+    }
+    for (; b < nblk; ++b) s += part[int64_t(b) * mlp::kTrainStride + i];
+    return s;
+}
+
 // Sums the nblk partials of mlp_train_kernel in block order into G (zero on
-// the untrained slots) and the mean loss, then one Adam step on [W1 .. b3].
+// the untrained slots) and the mean loss, then one Adam step on [W1 .. b3]
+// (b1c, b2c: the bias corrections 1 - beta^t).
 __global__ __launch_bounds__(256) void mlp_adam_kernel(float* __restrict__ P, float* __restrict__ G,
                                                        float* __restrict__ Am, float* __restrict__ Av,
                                                        const float* __restrict__ part, int nblk, float inv_b, float lr,
-                                                       int t, float* loss_out) {
+                                                       float b1c, float b2c, float* loss_out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i == mlp::kNParam) {
-        float sl = 0.f;
-        for (int b = 0; b < nblk; ++b) sl += part[int64_t(b) * mlp::kTrainStride + mlp::kNParam];
-        if (loss_out) *loss_out = sl * inv_b;
+        if (loss_out) *loss_out = train_sum(part, nblk, mlp::kNParam) * inv_b;
         return;
     }
     if (i > mlp::kNParam) return;
@@ -568,13 +612,12 @@ __global__ __launch_bounds__(256) void mlp_adam_kernel(float* __restrict__ P, fl
         G[i] = 0.f;
         return;
     }
-    float gi = 0.f;
-    for (int b = 0; b < nblk; ++b) gi += part[int64_t(b) * mlp::kTrainStride + i];
+    const float am = Am[i], av = Av[i], p = P[i];  // in flight with the partials
+    const float gi = train_sum(part, nblk, i);
     G[i] = gi;
-    const float b1c = 1.f - powf(0.9f, float(t)), b2c = 1.f - powf(0.999f, float(t));
-    const float m = 0.9f * Am[i] + 0.1f * gi;
-    const float v = 0.999f * Av[i] + 0.001f * gi * gi;
+    const float m = 0.9f * am + 0.1f * gi;
+    const float v = 0.999f * av + 0.001f * gi * gi;
     Am[i] = m;
     Av[i] = v;
-    P[i] -= lr * (m / b1c) / (sqrtf(v / b2c) + 1e-8f);
+    P[i] = p - lr * (m / b1c) / (sqrtf(v / b2c) + 1e-8f);
 }

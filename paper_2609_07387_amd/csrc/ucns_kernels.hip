@@ -1717,9 +1717,10 @@ int ucns_mlp_train_step(float* params, float* grads, float* adam_state, const fl
     float* part = static_cast<float*>(p);
     const int nblk = int(std::min<int64_t>((n + 63) / 64, mlp::kTrainMaxBlocks));
     const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(mlp_train_kernel, dim3(nblk), dim3(64), 0, s, params, part, features, labels, n, pos_weight);
+    const float b1c = 1.f - float(std::pow(double(0.9f), t)), b2c = 1.f - float(std::pow(double(0.999f), t));
+    hipLaunchKernelGGL(mlp_train_kernel, dim3(nblk), dim3(64 * mlp::kTrainWaves), 0, s, params, part, features, labels, n, pos_weight);
     hipLaunchKernelGGL(mlp_adam_kernel, dim3((mlp::kNParam + 256) / 256), dim3(256), 0, s, params, grads, adam_state,
-                       adam_state + mlp::kNParam, part, nblk, 1.f / float(n), lr, t, loss_dev);
+                       adam_state + mlp::kNParam, part, nblk, 1.f / float(n), lr, b1c, b2c, loss_dev);
     return hip_check("ucns_mlp_train_step");
 }
 
