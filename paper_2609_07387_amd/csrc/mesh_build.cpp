@@ -1040,6 +1040,26 @@ void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
             }
         }
     }
+    // where a cell's values lie: rows of the whole mesh at P2 and P3, tiles in
+    // lane order at P4 (kP4Tile)
+    const bool tiled = m.order == 4;
+    // value k of the KK values of member j (of `members`)
+    auto at_op = [&](int j, int members, int k, int KK, int64_t c) {
+        if (!tiled) return (size_t(j) * KK + k) * size_t(ns) + size_t(c);
+        const int slot = int(c % kP4Tile);
+        return (size_t(c / kP4Tile) * members + j) * KK * kP4Tile + (KK == 9 ? p4_pos<9>(k, slot) : p4_pos<kMaxK>(k, slot));
+    };
+    // id of member j of stencil st (of `stencils`, `members` each)
+    auto at_id = [&](int st, int j, int stencils, int members, int64_t c) {
+        if (!tiled) return (size_t(st) * members + j) * size_t(ns) + size_t(c);
+        return (size_t(c / kP4Tile) * stencils + st) * size_t(p4_ids(members)) * kP4Tile + size_t(j / 4) * 64 +
+               size_t(c % kP4Tile) * 4 + j % 4;
+    };
+    // axis d of face point p (of `points`)
+    auto at_xi = [&](int p, int points, int d, int64_t c) {
+        if (!tiled) return (size_t(p) * 3 + d) * size_t(ns) + size_t(c);
+        return size_t(c / kP4Tile) * points * 3 * kP4Tile + (size_t(p / 4) * 3 + d) * 64 + size_t(c % kP4Tile) * 4 + p % 4;
+    };
     std::vector<int> perm(kMaxCentral);
     for (int64_t c = 0; c < nc; ++c) {
         const int64_t* ids = &m.cand[size_t(c) * kMaxCentral];
@@ -1047,9 +1067,9 @@ void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
         for (int j = 0; j < n; ++j) perm[j] = j;
         std::sort(perm.begin(), perm.begin() + n, [&](int x, int y) { return ids[x] < ids[y]; });
         for (int j = 0; j < MC; ++j) {
-            sten_c[size_t(j) * ns + c] = j < n ? int32_t(ids[perm[j]]) : int32_t(c);
+            sten_c[at_id(0, j, 1, MC, c)] = j < n ? int32_t(ids[perm[j]]) : int32_t(c);
             for (int k = 0; k < K; ++k)  // member-major rows: (j, k) at (j K + k) nc
-                Bc[(size_t(j) * K + k) * ns + c] = j < n ? T(m.Bc[(size_t(c) * K + k) * MC + perm[j]]) : T(0);
+                Bc[at_op(j, MC, k, K, c)] = j < n ? T(m.Bc[(size_t(c) * K + k) * MC + perm[j]]) : T(0);
         }
         ndir[c] = uint8_t(m.ndir[c]);
         for (int s = 0; s < ND; ++s) {
@@ -1058,17 +1078,30 @@ void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
             for (int j = 0; j < nd; ++j) perm[j] = j;
             std::sort(perm.begin(), perm.begin() + nd, [&](int x, int y) { return dids[x] < dids[y]; });
             for (int j = 0; j < MD; ++j) {
-                sten_d[(size_t(s) * MD + j) * ns + c] = j < nd ? int32_t(dids[perm[j]]) : int32_t(c);
+                sten_d[at_id(s, j, ND, MD, c)] = j < nd ? int32_t(dids[perm[j]]) : int32_t(c);
                 for (int k = 0; k < KD; ++k)  // member-major rows: (s, j, k) at ((s MD + j) kd + k) nc
-                    Bd[((size_t(s) * MD + j) * KD + k) * ns + c] =
+                    Bd[at_op(s * MD + j, ND * MD, k, KD, c)] =
                         j < nd ? T(m.Bd[((size_t(c) * m.nd_max + s) * KD + k) * m.md_pad + perm[j]]) : T(0);
             }
         }
-        int t = 0;
-        if (reads_indicator_matrix(m.order, int(sizeof(T))))
+        const double* Oc = &m.O[size_t(c) * K * K];
+        if (tiled) {
+            // lane h of the cell's quad: its terms 4 i + h against its own and
+            // those of lane h ^ X (terms past the last are padding: zero)
+            for (int h = 0; h < 4; ++h)
+                for (int X = 0; X < 4; ++X)
+                    for (int j = 0; j < 9; ++j)
+                        for (int i = 0; i <= j; ++i) {
+                            const int g = 4 * i + h, g2 = 4 * j + (h ^ X);
+                            O[(size_t(c / kP4Tile) * kP4ORuns + p4_o_run(X, i, j)) * 64 + size_t(c % kP4Tile) * 4 + h] =
+                                g < K && g2 < K ? T(Oc[size_t(g) * K + g2]) : T(0);
+                        }
+        } else if (reads_indicator_matrix(m.order, int(sizeof(T)))) {
+            int t = 0;
             for (int k = 0; k < K; ++k)
-                for (int l = k; l < K; ++l) O[size_t(t++) * ns + c] = T(m.O[(size_t(c) * K + k) * K + l]);
-        th[c] = T(m.O[size_t(c) * K * K]);  // the linear block is its first entry times the identity
+                for (int l = k; l < K; ++l) O[size_t(t++) * ns + c] = T(Oc[size_t(k) * K + l]);
+        }
+        th[c] = T(Oc[0]);  // the linear block is its first entry times the identity
         if (m.order == 3) {
             int r = 0;
             for (int i = 4; i >= 0; --i)
@@ -1076,18 +1109,24 @@ void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
                     mom[size_t(r++) * ns + c] = T(m.moments[size_t(c) * m.nmom + mom_index(m.mom_deg, i, j, 4 - i - j)] /
                                                   (m.vol[c] * std::pow(m.hb[c], 4)));
         }
-        for (int k = 0; k < K; ++k) pmean[size_t(k) * ns + c] = T(m.mean[size_t(c) * K + k]);
+        for (int k = 0; k < K; ++k) pmean[at_op(0, 1, k, K, c)] = T(m.mean[size_t(c) * K + k]);
         for (int lf = 0; lf < NF; ++lf) {
             const int32_t fs = m.c2f[c * kMaxFaces + lf];
             c2f[size_t(lf) * ns + c] = fs;
             cnq[size_t(lf) * ns + c] = fs >= 0 ? uint8_t(m.fnq[fs >> 1]) : 0;
             for (int q = 0; q < Q; ++q)
                 for (int d = 0; d < 3; ++d)
-                    xi[((size_t(lf) * Q + q) * 3 + d) * ns + c] = T(m.xi[((size_t(c) * NF + lf) * Q + q) * 3 + d]);
+                    xi[at_xi(lf * Q + q, NF * Q, d, c)] = T(m.xi[((size_t(c) * NF + lf) * Q + q) * 3 + d]);
         }
         vol[c] = m.vol[c];
         hdt[c] = m.hdt[c];
     }
+    if (tiled)  // stencil slots past the last cell, and id rows past the last member, name a valid cell
+        for (int64_t c = 0; c < ns; ++c) {
+            for (int j = c < nc ? MC : 0; j < p4_ids(MC); ++j) sten_c[at_id(0, j, 1, MC, c)] = int32_t(nc - 1);
+            for (int st = 0; st < ND; ++st)
+                for (int j = c < nc ? MD : 0; j < p4_ids(MD); ++j) sten_d[at_id(st, j, ND, MD, c)] = int32_t(nc - 1);
+        }
     for (int64_t f = 0; f < nf; ++f) {
         fcell[2 * f] = int32_t(m.fcell[2 * f]);
         fcell[2 * f + 1] = int32_t(m.fcell[2 * f + 1]);
@@ -1114,12 +1153,14 @@ int pack_arena(const Mesh& m, int precision, Arena& a, std::vector<unsigned char
         off = align256(off + bytes);
         return o;
     };
-    a.sten_c = take(4 * MC * ns);
+    const bool tiled = m.order == 4;  // id rows padded to whole groups, O one run per load (kP4Tile)
+    a.sten_c = take(4 * (tiled ? size_t(p4_ids(int64_t(MC))) : MC) * ns);
     a.Bc = take(ts * K * MC * ns);
     a.ndir = take(nc);
-    a.sten_d = take(4 * ND * MD * ns);
+    a.sten_d = take(4 * ND * (tiled ? size_t(p4_ids(int64_t(MD))) : MD) * ns);
     a.Bd = take(ts * ND * m.kd * MD * ns);
-    a.O = take(reads_indicator_matrix(m.order, int(ts)) ? ts * K * (K + 1) / 2 * ns : 0);
+    a.O = take(tiled ? ts * kP4ORuns * 64 * (ns / kP4Tile)
+                     : reads_indicator_matrix(m.order, int(ts)) ? ts * K * (K + 1) / 2 * ns : 0);
     a.th = take(ts * nc);
     a.mom = take(ts * num_indicator_moments(m.order) * ns);
     a.xi = take(ts * NF * Q * 3 * ns);

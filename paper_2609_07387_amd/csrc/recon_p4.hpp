@@ -10,9 +10,9 @@
 // A quad of lanes per cell, 16 cells per wave.  Lane h of the quad owns the
 // basis terms g = 4 i + h (i = 0..8; terms 34 and 35 of lanes 2 and 3 are
 // padding held at zero) for all five variables: 45 coefficients per lane,
-// and every operator row a lane loads is its own (the four lanes of a quad
-// read four different rows of the cell's operator, so no value is fetched
-// twice).  The lanes' shares of a quadratic form or of a point value meet
+// and every operator value a lane loads is its own (no value is fetched
+// twice; the mesh arrays are stored tile by tile in the order the wave's lanes
+// read them, kP4Tile).  The lanes' shares of a quadratic form or of a point value meet
 // through quad DPP moves; each lane loads two of the five variables of a
 // stencil member's state and the quad broadcasts the other three.  Sums over
 // the quad are formed as (l0 + l1) + (l2 + l3) in every lane, so all four
@@ -24,12 +24,10 @@ constexpr int kP4Cells = 16;    // cells per wave
 constexpr int kP4Q = 16;        // Gauss points per quadrilateral face (4 x 4)
 constexpr int kP4T = 9;         // central terms per lane
 constexpr int kP4TD = 3;        // directional terms per lane (g = 4 i + h < 9)
-constexpr int kP4NO = kP4K * (kP4K + 1) / 2;  // rows of the upper triangle of O
-// Waves per SIMD the kernel is built for (FP64: 256 VGPRs; FP32: 168, a
-// few values spilled, measured faster than 2 waves without spills) and how
-// many members ahead of the arithmetic the operator rows load.
+// Waves per SIMD the kernel is built for (FP64: 256 VGPRs; FP32: 168) and how
+// many members ahead of the arithmetic the operator values load.
 constexpr int kP4Waves64 = 2, kP4Waves32 = 3;
-constexpr int kP4OpAhead64 = 1, kP4OpAhead32 = 1;
+constexpr int kP4OpAhead = 3;  // 1: 708 us against 693 (64,000 FP64 cells)
 
 // The 34 monomials of degree 1..4 in graded-lex order (x exponent
 // descending, then y) at a face point's scaled offset.
@@ -83,13 +81,6 @@ __device__ __forceinline__ T quad_sum(T x) {
     return p + quad_xor<2>(p);
 }
 
-// Row of O (upper triangle, row-major) of the term pair (p, q), p <= q;
-// rows past the last (padding terms) are clamped into the array.
-__device__ __forceinline__ int p4_tri(int p, int q) {
-    const int r = p * kP4K - (p * (p - 1)) / 2 + (q - p);
-    return r < kP4NO ? r : kP4NO - 1;
-}
-
 // Jumps of a stencil member's five variables, U_m - U_c in FP64 rounded to
 // T: lane k of the quad loaded variable k (broadcast to the quad), every
 // lane loaded variable 4.
@@ -104,7 +95,8 @@ __device__ __forceinline__ void p4_jumps(double uh, double u4, const double* ui,
 
 // The member stream of a list of stencils: member q (q = 0 .. n-1) has its
 // id at row q of `sten` and its KR operator rows at rows q KR .. of `op`
-// (each [row][cell]); the lane loads the rows at its byte offsets off[].
+// (the wave's tile, [row][16 cells]); the lane loads the rows at its byte
+// offsets off[].
 // body(q, bv, b) receives the member's five jumps and the lane's operator
 // values.  Loads run ahead of the arithmetic in 8-member trips with
 // compile-time register slots (no register is copied while its load is in
@@ -114,24 +106,21 @@ __device__ __forceinline__ void p4_jumps(double uh, double u4, const double* ui,
 //       (broadcast to the quad when used), 5 to 8 members ahead;
 //  states: 3 members ahead (4 slots of 2 values);
 //  operators: DB members ahead (DB + 1 slots, DB + 1 divides 8).
-// Rows past the last member read the last one, so every step issues the
-// same loads.
-template <class T, int NTL, int DB, class Body>
-__device__ __forceinline__ void p4_stream(const int32_t* sten, const T* op, int KR, int n, int64_t nc, uint32_t c4,
+// Members past the last read the last one, so every step issues the same
+// loads.
+template <class T, int NTL, int DB, bool STREAM, class Body>
+__device__ __forceinline__ void p4_stream(const int32_t* sten, const T* op, int KR, int n, uint32_t l4,
                                           const uint32_t* off, __amdgpu_buffer_rsrc_t rS, uint32_t hofs,
                                           const double* ui, int h, Body&& body) {
     constexpr int RB = DB + 1;
     static_assert(8 % RB == 0, "operator slots must divide the trip");
-    const uint32_t rowI = uint32_t(nc) * 4u;
-    auto group = [&](int g) {
-        const int r0 = min(4 * g, n - 1);
-        const int o = min(4 * g + h, n - 1) - r0;
-        return bld<int32_t>(row_rsrc(sten, r0, nc, 4), c4 + uint32_t(o) * rowI, 0u);
-    };
+    const auto rI = row_rsrc(sten, 0, 64, (n + 3) / 4), rB = row_rsrc(op, 0, kP4Cells, n * KR);
+    const uint32_t member = uint32_t(KR * kP4Cells) * uint32_t(sizeof(T));
+    auto group = [&](int g) { return bld<int32_t>(rI, l4, uint32_t(min(g, (n - 1) / 4)) * 256u); };
     auto load_b = [&](int q, T* b) {
-        const auto rB = row_rsrc(op, int64_t(min(q, n - 1)) * KR, nc, KR);
+        const uint32_t o = uint32_t(min(q, n - 1)) * member;
 #pragma unroll
-        for (int i = 0; i < NTL; ++i) b[i] = bld<T>(rB, off[i], 0u);
+        for (int i = 0; i < NTL; ++i) b[i] = blds<T, STREAM>(rB, off[i], o);
     };
     auto load_u = [&](int32_t j, double& uh, double& u4) {  // from the staged [cell][8] state
         uh = bld<double>(rS, uint32_t(j) * 64u + hofs, 0u);
@@ -168,26 +157,25 @@ __device__ __forceinline__ void p4_stream(const int32_t* sten, const T* op, int 
 }
 
 // One lane's share of the quadratic forms a_v^T O a_v (v = 0..4) over the
-// lane's NT terms g_i = 4 i + h, with tbase[i] the row of the pair (g_i, g_i):
-//  own pairs (i <= j): weight 1 on the diagonal, 2 off it, row
-//  tbase[i] + 4 (j - i);
-//  with lane h ^ X (partner term g'_j = 4 j + (h ^ X)): pairs i < j with
-//  weight 2 (g_i < g'_j, row tbase[i] + 4 (j - i) + (h ^ X) - h) and the
-//  diagonal pairs i = j with weight 2 in the lower lane of the two only.
-//  Summed over the quad every ordered pair of distinct terms counts once and
-//  each term's square once.
+// lane's NT terms g_i = 4 i + h:
+//  own pairs (i <= j) of g_i and g_j: weight 1 on the diagonal, 2 off it;
+//  with lane h ^ X (partner term g'_j = 4 j + (h ^ X)): pairs i < j of g_i and
+//  g'_j with weight 2, and the diagonal pairs i = j with weight 2 in the lower
+//  lane of the two only.
+// Summed over the quad every ordered pair of distinct terms counts once and
+// each term's square once.  O is stored in the order of these loads, one
+// 64-value run per load (p4_o_run): a lane reads its own entry at Ot[64 run].
 template <class T, int NT>
-__device__ __forceinline__ void p4_form_own(const T* __restrict__ O, int64_t nc, int64_t c, const int* tbase,
-                                            const T (*a)[NT], T* s) {
+__device__ __forceinline__ void p4_form_own(const T* __restrict__ Ot, const T (*a)[NT], T* s) {
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
         T t[5];
-        const T od = O[int64_t(tbase[i]) * nc + c];
+        const T od = Ot[64 * p4_o_run(0, i, i)];
 #pragma unroll
         for (int v = 0; v < 5; ++v) t[v] = od * a[v][i];
 #pragma unroll
         for (int j = i + 1; j < NT; ++j) {
-            const T o = T(2) * O[int64_t(min(tbase[i] + 4 * (j - i), kP4NO - 1)) * nc + c];
+            const T o = T(2) * Ot[64 * p4_o_run(0, i, j)];
 #pragma unroll
             for (int v = 0; v < 5; ++v) t[v] += o * a[v][j];
         }
@@ -197,11 +185,8 @@ __device__ __forceinline__ void p4_form_own(const T* __restrict__ O, int64_t nc,
 }
 
 template <int X, class T, int NT>
-__device__ __forceinline__ void p4_form_cross(const T* __restrict__ O, int64_t nc, int64_t c, int h, const int* tbase,
-                                              const T (*a)[NT], T* s) {
-    const int dh = (h ^ X) - h;
-    const T wdiag = dh > 0 ? T(2) : T(0);
-    const int ddiag = dh > 0 ? dh : 0;  // the upper lane reads a valid row it weights by zero
+__device__ __forceinline__ void p4_form_cross(const T* __restrict__ Ot, int h, const T (*a)[NT], T* s) {
+    const T wdiag = (h ^ X) > h ? T(2) : T(0);
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         T ap[5];  // the partner's coefficients of its term j
@@ -209,13 +194,13 @@ __device__ __forceinline__ void p4_form_cross(const T* __restrict__ O, int64_t n
         for (int v = 0; v < 5; ++v) ap[v] = quad_xor<X>(a[v][j]);
         T t[5];
         {
-            const T o = wdiag * O[int64_t(min(tbase[j] + ddiag, kP4NO - 1)) * nc + c];
+            const T o = wdiag * Ot[64 * p4_o_run(X, j, j)];
 #pragma unroll
             for (int v = 0; v < 5; ++v) t[v] = o * a[v][j];
         }
 #pragma unroll
         for (int i = 0; i < j; ++i) {
-            const T o = T(2) * O[int64_t(min(tbase[i] + 4 * (j - i) + dh, kP4NO - 1)) * nc + c];
+            const T o = T(2) * Ot[64 * p4_o_run(X, i, j)];
 #pragma unroll
             for (int v = 0; v < 5; ++v) t[v] += o * a[v][i];
         }
@@ -227,15 +212,14 @@ __device__ __forceinline__ void p4_form_cross(const T* __restrict__ O, int64_t n
 // a_v^T O a_v for the five variables, complete in every lane of the quad
 // (a sum of squares: a rounded value below zero is clamped).
 template <class T, int NT>
-__device__ __forceinline__ void p4_forms(const T* __restrict__ O, int64_t nc, int64_t c, int h, const int* tbase,
-                                         const T (*a)[NT], T* out) {
+__device__ __forceinline__ void p4_forms(const T* __restrict__ Ot, int h, const T (*a)[NT], T* out) {
     T s[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) s[v] = T(0);
-    p4_form_own<T, NT>(O, nc, c, tbase, a, s);
-    p4_form_cross<1, T, NT>(O, nc, c, h, tbase, a, s);
-    p4_form_cross<2, T, NT>(O, nc, c, h, tbase, a, s);
-    p4_form_cross<3, T, NT>(O, nc, c, h, tbase, a, s);
+    p4_form_own<T, NT>(Ot, a, s);
+    p4_form_cross<1, T, NT>(Ot, h, a, s);
+    p4_form_cross<2, T, NT>(Ot, h, a, s);
+    p4_form_cross<3, T, NT>(Ot, h, a, s);
 #pragma unroll
     for (int v = 0; v < 5; ++v) out[v] = fmax(quad_sum(s[v]), T(0));
 }
@@ -268,38 +252,42 @@ __global__ __launch_bounds__(kBlock) void p4_stage_state_kernel(const double* __
 //  (vi)  point values U_c + Phi_q . abar; positivity of rho and p at each point.
 // Every step per variable (component-wise).  LABEL: also the max over
 // stencils and variables of |omega - lambda| per cell.
-template <class T, bool LABEL>
+template <class T, bool LABEL, bool STREAM>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? kP4Waves32 : kP4Waves64)))
 void reconstruct_p4_kernel(ReconArgs<T> A) {
     constexpr int K = kP4K, KD = kP4KD, NT = kP4T, NTD = kP4TD;
     const int64_t nc = A.nc, ns = A.ns;
     const int lane = int(threadIdx.x & 63u);
     const int slot = lane >> 2, h = lane & 3;
-    const int64_t c0 = (xcd_block() * (kBlock / 64) + int64_t(threadIdx.x >> 6)) * kP4Cells;
+    // the wave's tile of 16 cells; the mesh arrays are [tile][row][16 cells],
+    // so that each load of four rows is one contiguous run
+    const int64_t tile = xcd_block() * (kBlock / 64) + __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const int64_t c0 = tile * kP4Cells;
     const bool valid = c0 + slot < nc;
-    // quads past the last cell shadow the wave's first cell (every load stays in range)
-    const int64_t c = valid ? c0 + slot : (c0 < nc ? c0 : nc - 1);
+    // the mesh arrays are padded to whole 64-cell tiles (their last ids name
+    // valid cells); a wave past those reads the last tile
+    const int64_t c = valid ? c0 + slot : nc - 1;
+    const int64_t tl = min(tile, (A.ns + kP4Cells - 1) / kP4Cells - 1);
+    const T* Ot = A.O + tl * kP4ORuns * 64 + lane;
+    const int32_t* sten_c = A.sten_c + tl * p4_ids(A.MC) * kP4Cells;
+    const T* Bc = A.Bc + tl * A.MC * K * kP4Cells;
+    const int32_t* sten_d = A.sten_d + tl * A.ND * p4_ids(A.MD) * kP4Cells;
+    const T* Bd = A.Bd + tl * A.ND * A.MD * KD * kP4Cells;
+    const T* pmean = A.pmean + tl * K * kP4Cells;
+    const T* xi = A.xi + tl * A.NF * A.Q * 3 * kP4Cells + lane;
     double ui[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) ui[v] = A.U[v * nc + c];
-    // Stencil streams are buffer loads: the member's rows in a scalar
-    // descriptor, the lane's byte offset in a 32-bit register (the launcher
-    // bounds every such span below 4 GiB).
-    const uint32_t cT = uint32_t(c) * uint32_t(sizeof(T)), c4 = uint32_t(c) * 4u;
-    const uint32_t rowT = uint32_t(ns) * uint32_t(sizeof(T));
+    // Stencil streams are buffer loads: the tile's rows in a scalar
+    // descriptor, the lane's byte offset in a 32-bit register.
+    const uint32_t l4 = uint32_t(lane) * 4u;
     const auto rS = rsrc(A.ustage, uint64_t(nc) * 64u);  // the staged [cell][8] state
     const uint32_t hofs = uint32_t(h) * 8u;              // the lane's variable in a cell's record
-    // operator rows of the lane's terms (padding terms read the last row),
-    // as byte offsets, and their diagonal rows of O
-    int trow[NT], tbase[NT];
+    // the lane's terms as byte offsets in a member's block of K x 16 values,
+    // stored in lane order (p4_pos): padding terms read the last one
     uint32_t toff[NT];
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
-        const int g = 4 * i + h < K ? 4 * i + h : K;
-        trow[i] = g < K ? g : K - 1;
-        tbase[i] = p4_tri(g, g);
-        toff[i] = cT + uint32_t(trow[i]) * rowT;
-    }
+    for (int i = 0; i < NT; ++i) toff[i] = uint32_t(p4_pos<K>(min(4 * i + h, K - 1), slot)) * uint32_t(sizeof(T));
 
     // (ii) central coefficients; member m's id at sten_c[m][c], its K
     // operator rows at Bc[m][k][c].
@@ -308,7 +296,7 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
     for (int v = 0; v < 5; ++v)
 #pragma unroll
         for (int i = 0; i < NT; ++i) a[v][i] = T(0);
-    p4_stream<T, NT, sizeof(T) == 4 ? kP4OpAhead32 : kP4OpAhead64>(A.sten_c, A.Bc, K, A.MC, ns, c4, toff, rS, hofs, ui, h,
+    p4_stream<T, NT, kP4OpAhead, STREAM>(sten_c, Bc, K, A.MC, l4, toff, rS, hofs, ui, h,
                                              [&](int, const T* bv, const T* b) {
 #pragma unroll
                                                  for (int v = 0; v < 5; ++v)
@@ -322,7 +310,7 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
 
     // (iii) SI_1 = a^T O a
     T SI1[5];
-    p4_forms<T, NT>(A.O, ns, c, h, tbase, a, SI1);
+    p4_forms<T, NT>(Ot, h, a, SI1);
     // the terms of degree 3 and 4 (i >= 3) take no part in the directional
     // step: parked in LDS (each lane its own slots) until the blend
     __shared__ T park[kBlock / 64][5 * (NT - NTD)][64];
@@ -350,9 +338,9 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
         }
     }
     if (nd > 0) {  // uniform within a quad
-        uint32_t doff[NTD];  // the lane's directional operator rows as byte offsets
+        uint32_t doff[NTD];  // the lane's directional operator values as byte offsets
 #pragma unroll
-        for (int i = 0; i < NTD; ++i) doff[i] = cT + uint32_t(4 * i + h < KD ? 4 * i + h : KD - 1) * rowT;
+        for (int i = 0; i < NTD; ++i) doff[i] = uint32_t(p4_pos<KD>(min(4 * i + h, KD - 1), slot)) * uint32_t(sizeof(T));
         const int MD = A.MD;
 #pragma unroll 1
         for (int s = 0; s < A.ND; ++s) {
@@ -361,8 +349,8 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
             for (int v = 0; v < 5; ++v)
 #pragma unroll
                 for (int i = 0; i < NTD; ++i) as[v][i] = T(0);
-            p4_stream<T, NTD, sizeof(T) == 4 ? kP4OpAhead32 : kP4OpAhead64>(A.sten_d + int64_t(s) * MD * ns, A.Bd + int64_t(s) * MD * KD * ns,
-                                                      KD, MD, ns, c4, doff, rS, hofs, ui, h,
+            p4_stream<T, NTD, kP4OpAhead, STREAM>(sten_d + s * p4_ids(MD) * kP4Cells, Bd + s * MD * KD * kP4Cells,
+                                                      KD, MD, l4, doff, rS, hofs, ui, h,
                                                       [&](int, const T* bv, const T* b) {
 #pragma unroll
                                                           for (int v = 0; v < 5; ++v)
@@ -376,7 +364,7 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
             if (s < nd) {
                 // SI_s with the block of O on the first KD terms
                 T SIs[5];
-                p4_forms<T, NTD>(A.O, ns, c, h, tbase, as, SIs);
+                p4_forms<T, NTD>(Ot, h, as, SIs);
 #pragma unroll
                 for (int v = 0; v < 5; ++v) {
                     tsum[v] += fabs(SI1[v] - SIs[v]);
@@ -425,7 +413,7 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
     // lane h writes variable h, lane 0 also variable 4
     T pm[NT];
 #pragma unroll
-    for (int i = 0; i < NT; ++i) pm[i] = A.pmean[int64_t(trow[i]) * ns + c];
+    for (int i = 0; i < NT; ++i) pm[i] = pmean[p4_pos<K>(min(4 * i + h, K - 1), slot)];
     bool ok = true;
     // The face points as one sequence p = lf Q + q, in trips of 8 points.
     // Offsets load four points per instruction (lane h of the quad takes
@@ -434,10 +422,10 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
     const int Q = A.Q, NP = A.NF * A.Q;
     auto group = [&](int g, T* xo, int& nq) {
         const int pp = min(4 * g + h, NP - 1);
-        const T* X = A.xi + int64_t(pp) * 3 * ns + c;
+        const T* X = xi + min(g, NP / 4 - 1) * 3 * 64;  // [group of 4 points][axis][lane] (NP is a multiple of 4)
         xo[0] = X[0];
-        xo[1] = X[ns];
-        xo[2] = X[2 * ns];
+        xo[1] = X[64];
+        xo[2] = X[128];
         nq = A.cnq[int64_t(pp / Q) * ns + c];
     };
     auto point = [&](int p, T x, T y, T z) {

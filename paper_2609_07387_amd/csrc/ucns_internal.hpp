@@ -53,14 +53,40 @@ constexpr uint64_t kMaxDescriptorBytes = 0xffffffffull;
 // two hold it, and the streamed lines shared with the next wave be fetched
 // twice); the plain count where the padding would push a descriptor past its
 // limit.
+// P4: a wave takes a tile of 16 cells with a quad of lanes per cell, lane
+// 4 slot + h owning the basis terms 4 i + h.  Its arrays are stored tile by tile
+// in the order the wave's lanes read them, so that each load is one contiguous
+// run.  The vector memory path merges neighbouring lanes only: with the four
+// lanes of a quad reading four rows a load took 64 cache accesses where 8 do,
+// and the path was busy 91 % of the call (47 accesses per load on average, 17
+// now).  64,000 FP64 cells 853 -> 694 us, 9,975 FP32 cells 162 -> 126 us.
+//  a member's K operator values (K = 34 or 9; also the basis means): p4_pos;
+//  member ids: groups of four members, lane h holding the group's member h;
+//  face points: groups of four points, [axis][lane], likewise;
+//  the indicator matrix: one run of 64 per load of the form (p4_o_run).
+constexpr int64_t kP4Tile = 16;
+template <int K>
+constexpr int p4_pos(int g, int slot) {
+    return g / 4 < K / 4 ? (g / 4) * 64 + slot * 4 + g % 4 : (K / 4) * 64 + slot * (K % 4) + g % 4;
+}
+constexpr int64_t p4_ids(int64_t members) { return (members + 3) / 4 * 4; }  // id rows of a stencil
+// Run of the load of O's entry for the own pair (i, j), i <= j (X = 0), or for
+// the lane's term i and term j of lane h ^ X, i <= j (X = 1..3), of the lane's
+// nine terms.  Pairs with j < 3 (the degree <= 2 block that the directional
+// indicators use) come first.
+constexpr int kP4ORuns = 4 * 45;
+constexpr int p4_o_run(int X, int i, int j) {
+    return j < 3 ? X * 6 + j * (j + 1) / 2 + i : 24 + X * 39 + (j * (j + 1) / 2 - 6) + i;
+}
 inline int64_t row_stride(int64_t nc, int K) {
     const int64_t padded = fs_cells_padded(nc);
+    if (K == kMaxK) return padded;  // whole tiles
     return uint64_t(std::max(K, 5)) * 8u * uint64_t(padded) <= kMaxDescriptorBytes ? padded : nc;
 }
 
 
 // Offsets (bytes) of every array inside one precision's device arena (per-cell
-// arrays [row][ns], ns = Mesh::ns).
+// arrays [row][ns], ns = Mesh::ns; P4's operators in tiles, kP4Tile).
 struct Arena {
     size_t bytes = 0;
     size_t sten_c = 0, Bc = 0, ndir = 0, sten_d = 0, Bd = 0, O = 0, xi = 0, pmean = 0, c2f = 0;

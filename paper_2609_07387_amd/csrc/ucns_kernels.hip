@@ -1119,19 +1119,26 @@ int launch_recon_k(const ReconArgs<T>& A, hipStream_t st, bool grad_lsq = false)
     return UCNS_OK;
 }
 
-// P4: one lane per (cell, variable), 12 cells per wave; full CWENOZ only
+// P4: a quad of lanes per cell, 16 cells per wave; full CWENOZ only
 // (the gate's network is trained on P2 features).
 template <class T>
 int launch_recon_p4(const ReconArgs<T>& A, hipStream_t st) {
     if (A.Q > kP4Q || A.NF > kMaxFaces || A.mlp || A.gate || !A.ustage) return UCNS_EINVAL;
     if (recon_span_bytes(A.nc, int(sizeof(T)), kP4K, A.NF) > kMaxDescriptorBytes) return UCNS_EINVAL;
     hipLaunchKernelGGL(p4_stage_state_kernel, dim3(grid_for(A.nc)), dim3(kBlock), 0, st, A.U, A.nc, A.ustage);
+    static_assert(kP4Cells == kP4Tile);
     const int64_t per_block = int64_t(kBlock / 64) * kP4Cells;
     const dim3 grid(unsigned((A.nc + per_block - 1) / per_block)), block(kBlock);
+    // (nt_streams' rule: 9,975 FP32 cells, 156 MB, 138 us plain and 161 marked;
+    // 64,000 FP64 cells 713 and 708 us)
+    const int64_t t = sizeof(T);
+    const bool nt = A.ns * t * (kP4K * A.MC + kP4KD * A.ND * A.MD) > kInfinityCache - (int64_t(6) << 20);
     if (A.label)
-        hipLaunchKernelGGL((reconstruct_p4_kernel<T, true>), grid, block, 0, st, A);
+        hipLaunchKernelGGL((reconstruct_p4_kernel<T, true, false>), grid, block, 0, st, A);
+    else if (nt)
+        hipLaunchKernelGGL((reconstruct_p4_kernel<T, false, true>), grid, block, 0, st, A);
     else
-        hipLaunchKernelGGL((reconstruct_p4_kernel<T, false>), grid, block, 0, st, A);
+        hipLaunchKernelGGL((reconstruct_p4_kernel<T, false, false>), grid, block, 0, st, A);
     hipLaunchKernelGGL((reconstruct_p4_fallback_kernel<T>), dim3(grid_for(A.nc)), block, 0, st, A);
     return UCNS_OK;
 }
