@@ -1139,8 +1139,9 @@ __device__ __forceinline__ bool recon_cell(const ReconArgs<T>& A, int64_t c, con
 // flag for the fallback pass.  GRAD (1 Green-Gauss, 2 least squares): the
 // cell then forms its gradient of W as well (the positivity fallback changes
 // point states only, never the cell averages the gradient is taken from).
-template <class T, int K, bool LABEL, bool GATE, int GRAD, bool NT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
+// WB waves per block (recon_block_waves).
+template <class T, int K, bool LABEL, bool GATE, int GRAD, bool NT, int WB>
+__global__ __launch_bounds__(64 * WB) __attribute__((amdgpu_waves_per_eu(
     K == 9 && (sizeof(T) == 4 ? GATE : !GATE && !LABEL) ? (sizeof(T) == 4 ? 3 : 2) : 1)))
 void reconstruct_kernel(ReconArgs<T> A) {
     const int64_t c = xcd_block() * blockDim.x + threadIdx.x;
@@ -1158,7 +1159,7 @@ void reconstruct_kernel(ReconArgs<T> A) {
         constexpr int kStage = stage_points<K>() * 320 * int(sizeof(T));  // then the point-state staging
         constexpr int kWaveLds0 = sizeof(MlpWaveLds) > kStash ? int(sizeof(MlpWaveLds)) : kStash;
         constexpr int kWaveLds = kWaveLds0 > kStage ? kWaveLds0 : kStage;
-        __shared__ __attribute__((aligned(16))) unsigned char lds[kBlock / 64][kWaveLds];
+        __shared__ __attribute__((aligned(16))) unsigned char lds[WB][kWaveLds];
         unsigned char* wl = lds[threadIdx.x >> 6];
         if (A.mlp) {
             const float* fv = reinterpret_cast<const float*>(A.mlp + mlpimg::kF);
@@ -1208,7 +1209,7 @@ void reconstruct_kernel(ReconArgs<T> A) {
         A.flags[c] = uint8_t((mode == 0 ? 1 : 0) | (ok ? 0 : 0x80));
         if constexpr (GRAD != 0) cell_gradient<T, GRAD == 2, NT>(A, c, ui);
     } else {
-        __shared__ T stage[kBlock / 64][stage_points<K>() * 320];
+        __shared__ T stage[WB][stage_points<K>() * 320];
         if (!valid) return;
 #pragma unroll
         for (int v = 0; v < 5; ++v) ui[v] = A.U[v * A.nc + c];

@@ -252,8 +252,9 @@ __global__ __launch_bounds__(kBlock) void p4_stage_state_kernel(const double* __
 //  (vi)  point values U_c + Phi_q . abar; positivity of rho and p at each point.
 // Every step per variable (component-wise).  LABEL: also the max over
 // stencils and variables of |omega - lambda| per cell.
-template <class T, bool LABEL, bool STREAM>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? kP4Waves32 : kP4Waves64)))
+// WB waves per block.
+template <class T, bool LABEL, bool STREAM, int WB>
+__global__ __launch_bounds__(64 * WB) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? kP4Waves32 : kP4Waves64)))
 void reconstruct_p4_kernel(ReconArgs<T> A) {
     constexpr int K = kP4K, KD = kP4KD, NT = kP4T, NTD = kP4TD;
     const int64_t nc = A.nc, ns = A.ns;
@@ -261,7 +262,7 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
     const int slot = lane >> 2, h = lane & 3;
     // the wave's tile of 16 cells; the mesh arrays are [tile][row][16 cells],
     // so that each load of four rows is one contiguous run
-    const int64_t tile = xcd_block() * (kBlock / 64) + __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const int64_t tile = xcd_block() * WB + __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const int64_t c0 = tile * kP4Cells;
     const bool valid = c0 + slot < nc;
     // the mesh arrays are padded to whole 64-cell tiles (their last ids name
@@ -313,7 +314,7 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
     p4_forms<T, NT>(Ot, h, a, SI1);
     // the terms of degree 3 and 4 (i >= 3) take no part in the directional
     // step: parked in LDS (each lane its own slots) until the blend
-    __shared__ T park[kBlock / 64][5 * (NT - NTD)][64];
+    __shared__ T park[WB][5 * (NT - NTD)][64];
     const int wv = int(threadIdx.x >> 6);
 #pragma unroll
     for (int v = 0; v < 5; ++v)

@@ -960,6 +960,10 @@ __global__ __launch_bounds__(kBlock) void diss_final_kernel(int nb, const double
 
 // ----------------------------------------------------------------- helpers
 
+// Threads per block of a kernel of independent lanes: one-wave blocks for a
+// call of at most one wave per SIMD, so that it reaches every CU.
+inline unsigned block_for(int64_t n) { return n <= 65536 ? 64 : kBlock; }
+
 inline unsigned grid_for(int64_t n) { return unsigned((n + kBlock - 1) / kBlock); }
 
 int hip_check(const char* what) {
@@ -1072,9 +1076,35 @@ bool nt_streams(const ReconArgs<T>& A, int K) {
     return A.ns * (central + dir + t * 3 * A.NF * A.Q + slots) > kInfinityCache - (int64_t(6) << 20);
 }
 
-template <class T, int K, bool NT>
-int launch_recon_main(const ReconArgs<T>& A, hipStream_t st, bool grad_lsq) {
-    const dim3 grid(grid_for(A.nc)), block(kBlock);
+// Waves per block of a reconstruction call.  One-wave blocks spread over the
+// CUs when the call does not fill them (at most 2,048 waves, two per SIMD;
+// 4,096 FP64 cells 46 -> 35 us, 13,122 P3 FP32 tets 50 -> 39 us, 44,574 61 ->
+// 57 us, 27,000 P3 FP64 hexahedra 157 -> 136 us), and free their slots one by
+// one when the waves' work differs: gated (375,000 shocked tets 207 -> 196 us)
+// or with stencils of several sizes (mixed FP64 right-hand side 432 -> 421 us).
+// Four waves share a CU's cache when the call is large and even (64^3 FP64 302
+// against 307 us, 196,608 P3 FP64 tets 397 against 411 us).
+inline int recon_block_waves(int64_t waves, bool uneven) { return waves <= 2048 || uneven ? 1 : 4; }
+
+template <class T, int K, bool GATE, int GRAD>
+void launch_recon_main(const ReconArgs<T>& A, hipStream_t st) {
+    const int64_t waves = (A.nc + 63) / 64;
+    const bool nt = nt_streams(A, K);
+    // (streams that fit the Infinity Cache are those of small or gated calls)
+    const bool one = !nt || recon_block_waves(waves, GATE || A.MCmin < A.MC) == 1;
+    const dim3 g1{unsigned(waves)}, g4{unsigned((waves + 3) / 4)};
+    if (!nt)
+        hipLaunchKernelGGL((reconstruct_kernel<T, K, false, GATE, GRAD, false, 1>), g1, dim3(64), 0, st, A);
+    else if (GATE || one)
+        hipLaunchKernelGGL((reconstruct_kernel<T, K, false, GATE, GRAD, true, 1>), g1, dim3(64), 0, st, A);
+    else if constexpr (!GATE)
+        hipLaunchKernelGGL((reconstruct_kernel<T, K, false, GATE, GRAD, true, 4>), g4, dim3(256), 0, st, A);
+}
+
+template <class T, int K>
+int launch_recon_k(const ReconArgs<T>& A, hipStream_t st, bool grad_lsq = false) {
+    if (A.Q > face_qmax<K>()) return UCNS_EINVAL;
+    if (recon_span_bytes(A.nc, int(sizeof(T)), K, A.NF) > kMaxDescriptorBytes) return UCNS_EINVAL;
     const bool gate = A.mlp || A.gate;
     if (A.gradW) {
         // the fused gradients (grad_lsq: least squares, else Green-Gauss): P2
@@ -1083,38 +1113,25 @@ int launch_recon_main(const ReconArgs<T>& A, hipStream_t st, bool grad_lsq) {
         if constexpr (K == 9) {
             if (A.label) return UCNS_EINVAL;
             if (grad_lsq && gate)
-                hipLaunchKernelGGL((reconstruct_kernel<T, K, false, true, 2, NT>), grid, block, 0, st, A);
+                launch_recon_main<T, K, true, 2>(A, st);
             else if (grad_lsq)
-                hipLaunchKernelGGL((reconstruct_kernel<T, K, false, false, 2, NT>), grid, block, 0, st, A);
+                launch_recon_main<T, K, false, 2>(A, st);
             else if (gate)
-                hipLaunchKernelGGL((reconstruct_kernel<T, K, false, true, 1, NT>), grid, block, 0, st, A);
+                launch_recon_main<T, K, true, 1>(A, st);
             else
-                hipLaunchKernelGGL((reconstruct_kernel<T, K, false, false, 1, NT>), grid, block, 0, st, A);
+                launch_recon_main<T, K, false, 1>(A, st);
         } else {
             return UCNS_EINVAL;
         }
     } else if (gate) {
-        hipLaunchKernelGGL((reconstruct_kernel<T, K, false, true, 0, NT>), grid, block, 0, st, A);
+        launch_recon_main<T, K, true, 0>(A, st);
+    } else if (A.label) {
+        // (serves the gate's data collection only)
+        hipLaunchKernelGGL((reconstruct_kernel<T, K, true, false, 0, false, 4>), dim3(grid_for(A.nc)), dim3(kBlock), 0,
+                           st, A);
     } else {
-        if constexpr (!NT) {
-            if (A.label) {
-                hipLaunchKernelGGL((reconstruct_kernel<T, K, true, false, 0, false>), grid, block, 0, st, A);
-                return UCNS_OK;
-            }
-        }
-        hipLaunchKernelGGL((reconstruct_kernel<T, K, false, false, 0, NT>), grid, block, 0, st, A);
+        launch_recon_main<T, K, false, 0>(A, st);
     }
-    return UCNS_OK;
-}
-
-template <class T, int K>
-int launch_recon_k(const ReconArgs<T>& A, hipStream_t st, bool grad_lsq = false) {
-    if (A.Q > face_qmax<K>()) return UCNS_EINVAL;
-    if (recon_span_bytes(A.nc, int(sizeof(T)), K, A.NF) > kMaxDescriptorBytes) return UCNS_EINVAL;
-    // (the labelled variant serves the gate's data collection only)
-    const int rc = nt_streams(A, K) && !A.label ? launch_recon_main<T, K, true>(A, st, grad_lsq)
-                                    : launch_recon_main<T, K, false>(A, st, grad_lsq);
-    if (rc != UCNS_OK) return rc;
     hipLaunchKernelGGL((reconstruct_fallback_kernel<T, K>), dim3(grid_for(A.nc)), dim3(kBlock), 0, st, A);
     return UCNS_OK;
 }
@@ -1127,19 +1144,19 @@ int launch_recon_p4(const ReconArgs<T>& A, hipStream_t st) {
     if (recon_span_bytes(A.nc, int(sizeof(T)), kP4K, A.NF) > kMaxDescriptorBytes) return UCNS_EINVAL;
     hipLaunchKernelGGL(p4_stage_state_kernel, dim3(grid_for(A.nc)), dim3(kBlock), 0, st, A.U, A.nc, A.ustage);
     static_assert(kP4Cells == kP4Tile);
-    const int64_t per_block = int64_t(kBlock / 64) * kP4Cells;
-    const dim3 grid(unsigned((A.nc + per_block - 1) / per_block)), block(kBlock);
     // (nt_streams' rule: 9,975 FP32 cells, 156 MB, 138 us plain and 161 marked;
-    // 64,000 FP64 cells 713 and 708 us)
-    const int64_t t = sizeof(T);
+    // 64,000 FP64 cells 713 and 708 us; one-wave blocks for the calls that fit
+    // the cache, 1,485 FP32 cells 120 -> 114 us)
+    const int64_t t = sizeof(T), waves = (A.nc + kP4Cells - 1) / kP4Cells;
     const bool nt = A.ns * t * (kP4K * A.MC + kP4KD * A.ND * A.MD) > kInfinityCache - (int64_t(6) << 20);
+    const dim3 g1{unsigned(waves)}, g4{unsigned((waves + 3) / 4)};
     if (A.label)
-        hipLaunchKernelGGL((reconstruct_p4_kernel<T, true, false>), grid, block, 0, st, A);
-    else if (nt)
-        hipLaunchKernelGGL((reconstruct_p4_kernel<T, false, true>), grid, block, 0, st, A);
+        hipLaunchKernelGGL((reconstruct_p4_kernel<T, true, false, 4>), g4, dim3(256), 0, st, A);
+    else if (!nt)
+        hipLaunchKernelGGL((reconstruct_p4_kernel<T, false, false, 1>), g1, dim3(64), 0, st, A);
     else
-        hipLaunchKernelGGL((reconstruct_p4_kernel<T, false, false>), grid, block, 0, st, A);
-    hipLaunchKernelGGL((reconstruct_p4_fallback_kernel<T>), dim3(grid_for(A.nc)), block, 0, st, A);
+        hipLaunchKernelGGL((reconstruct_p4_kernel<T, false, true, 4>), g4, dim3(256), 0, st, A);
+    hipLaunchKernelGGL((reconstruct_p4_fallback_kernel<T>), dim3(grid_for(A.nc)), dim3(kBlock), 0, st, A);
     return UCNS_OK;
 }
 
@@ -1474,8 +1491,9 @@ int ucns_face_flux(const ucns_mesh* mesh, const ucns_phys* phys, const ucns_bc* 
                       arena_ptr<uint8_t>(ar, ar.flf), arena_ptr<T>(ar, ar.fnrm), arena_ptr<T>(ar, ar.farea), arena_ptr<T>(ar, ar.fw),
                       arena_ptr<T>(ar, ar.fdc), arena_ptr<uint8_t>(ar, ar.fnq), static_cast<const T*>(gradW),
                       static_cast<T*>(face_flux)};
-        hipLaunchKernelGGL((face_flux_kernel<T>), dim3(grid_for(m.nf)), dim3(kBlock), 0, st, A, make_phys<T>(phys),
-                           make_bc<T>(bc));
+        const unsigned bl = block_for(m.nf);
+        hipLaunchKernelGGL((face_flux_kernel<T>), dim3(unsigned((m.nf + bl - 1) / bl)), dim3(bl), 0, st, A,
+                           make_phys<T>(phys), make_bc<T>(bc));
     };
     if (precision == UCNS_F64)
         go(double(0));
@@ -1497,10 +1515,11 @@ int launch_residual(const ucns_mesh* mesh, const void* face_flux, int precision,
         ResArgs<T> A{static_cast<const T*>(face_flux), m.nc, m.ns, arena_ptr<int32_t>(ar, ar.c2f), m.nfmax,
                      arena_ptr<double>(ar, ar.vol), R, U0, U, dt_dev, stage >= 0 ? Ac[stage] : 0.0,
                      stage >= 0 ? Bc_[stage] : 0.0, stage};
+        const unsigned bl = block_for(m.nc);
         if (stage >= 0)
-            hipLaunchKernelGGL((residual_kernel<T, true>), dim3(grid_for(m.nc)), dim3(kBlock), 0, st, A);
+            hipLaunchKernelGGL((residual_kernel<T, true>), dim3(unsigned((m.nc + bl - 1) / bl)), dim3(bl), 0, st, A);
         else
-            hipLaunchKernelGGL((residual_kernel<T, false>), dim3(grid_for(m.nc)), dim3(kBlock), 0, st, A);
+            hipLaunchKernelGGL((residual_kernel<T, false>), dim3(unsigned((m.nc + bl - 1) / bl)), dim3(bl), 0, st, A);
     };
     if (precision == UCNS_F64)
         go(double(0));
@@ -1540,7 +1559,8 @@ int ucns_residual_ssp54_stage(const ucns_mesh* mesh, const void* face_flux, int 
         using T = decltype(zero);
         ResArgs<T> A{static_cast<const T*>(face_flux), m.nc, m.ns, arena_ptr<int32_t>(ar, ar.c2f), m.nfmax,
                      arena_ptr<double>(ar, ar.vol), nullptr, nullptr, U, dt_dev, 0.0, 0.0, stage};
-        hipLaunchKernelGGL(residual_ssp54_kernel<T>, dim3(grid_for(m.nc)), dim3(kBlock), 0, st, A, W);
+        const unsigned bl = block_for(m.nc);
+        hipLaunchKernelGGL(residual_ssp54_kernel<T>, dim3(unsigned((m.nc + bl - 1) / bl)), dim3(bl), 0, st, A, W);
     };
     if (precision == UCNS_F64)
         go(double(0));
