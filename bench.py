@@ -34,7 +34,9 @@ def recon_kernels(head, grad):
     grad: the gradients the main pass also forms (0 none, 1 Green-Gauss,
     2 least squares)."""
     t, g = ("float", "true") if head == "fp32_gate" else ("double", "false")
-    return f"reconstruct_kernel<{t}, 9, false, {g}, {grad}|reconstruct_fallback_kernel<{t}, 9>"
+    main = f"reconstruct_kernel<{t}, 9, false, {g}, {grad}"
+    # (without a gate the main pass finishes the cells that violate positivity)
+    return main + (f"|reconstruct_fallback_kernel<{t}, 9>" if head == "fp32_gate" else "")
 
 
 

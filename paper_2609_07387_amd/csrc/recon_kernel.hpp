@@ -1119,6 +1119,23 @@ __device__ __forceinline__ bool recon_cell(const ReconArgs<T>& A, int64_t c, con
     return face_values<T, K, STAGE, NT>(A, c, ui, mode, a, stage);
 }
 
+// First order at a cell's own face points (its average), the positivity
+// fallback of a cell that has taken full CWENOZ.
+template <class T>
+__device__ __forceinline__ void first_order_points(const ReconArgs<T>& A, int64_t c, const double* ui) {
+    const int64_t ncp = fs_cells_padded(A.nc);
+#pragma unroll 1
+    for (int lf = 0; lf < A.NF; ++lf) {
+        const int nq = A.cnq[int64_t(lf) * A.ns + c];
+#pragma unroll 1
+        for (int q = 0; q < nq; ++q) {
+            T* out = A.fs + ((int64_t(lf) * A.Q + q) * ncp + c) * 5;
+#pragma unroll
+            for (int v = 0; v < 5; ++v) out[v] = T(ui[v]);
+        }
+    }
+}
+
 // Main pass without a gate (full CWENOZ everywhere), or with a gate (a mask,
 // or the troubled-cell network run inside this kernel).
 //
@@ -1135,8 +1152,10 @@ __device__ __forceinline__ bool recon_cell(const ReconArgs<T>& A, int64_t c, con
 // The FP32 P2 variant is held to 3 waves per SIMD, which its LDS already
 // imposes.
 //
-// A cell whose point states violate positivity is marked with bit 7 of its
-// flag for the fallback pass.  GRAD (1 Green-Gauss, 2 least squares): the
+// A gated cell whose point states violate positivity is marked with bit 7 of its
+// flag for the fallback pass.  Without a gate such a cell has taken full CWENOZ
+// and falls back to first order here (the pass cost its launch, 4.5 us a call:
+// 64^3 FP64 call 302 -> 298 us, 44,574 P3 FP32 tets 56.8 -> 55.1 us).  GRAD (1 Green-Gauss, 2 least squares): the
 // cell then forms its gradient of W as well (the positivity fallback changes
 // point states only, never the cell averages the gradient is taken from).
 // WB waves per block (recon_block_waves).
@@ -1216,7 +1235,11 @@ void reconstruct_kernel(ReconArgs<T> A) {
         central_coeffs<T, K, false, NT>(A, c, ui, a, nullptr, MCw);
         float lab = 0.f;
         const bool ok = recon_cell<T, K, LABEL, true, NT>(A, c, ui, 1, lab, a, stage[threadIdx.x >> 6]);
-        A.flags[c] = uint8_t(ok ? 0 : 0x80);
+        if (!ok) {
+            __threadfence();  // after the wave's staged stores of these points
+            first_order_points<T>(A, c, ui);
+        }
+        A.flags[c] = uint8_t(ok ? 0 : 4);
         if constexpr (LABEL) A.label[c] = lab;
         if constexpr (GRAD != 0) cell_gradient<T, GRAD == 2, NT>(A, c, ui);
     }
@@ -1238,8 +1261,9 @@ __global__ __launch_bounds__(kBlock) void gate_features_kernel(ReconArgs<T> A, f
     for (int k = 0; k < 12; ++k) out[c * 12 + k] = f[k];
 }
 
-// Fallback pass over the marked cells: gated-linear -> full CWENOZ -> first
-// order, rewriting the cell's point states (bit1 / bit2 record the steps).
+// Fallback pass over the marked cells of a gated call: gated-linear -> full
+// CWENOZ -> first order, rewriting the cell's point states (bit1 / bit2 record
+// the steps).
 template <class T, int K>
 __global__ __launch_bounds__(kBlock) void reconstruct_fallback_kernel(ReconArgs<T> A) {
     const int64_t c = xcd_block() * blockDim.x + threadIdx.x;

@@ -473,25 +473,18 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
         });
     }
     if (valid && h == 0) {
-        A.flags[c] = uint8_t(ok ? 0 : 0x80);
+        // positivity: the pass is full CWENOZ, so a cell with a bad point falls
+        // back to first order (its average at every own face point; bit 2)
+        if (!ok) {
+            __threadfence();  // after the quad's stores of these points
+            for (int p = 0; p < NP; ++p) {
+                if (p - (p / Q) * Q >= A.cnq[int64_t(p / Q) * ns + c]) continue;
+                T* out = A.fs + (int64_t(p) * fs_cells_padded(nc) + c) * 5;
+#pragma unroll
+                for (int v = 0; v < 5; ++v) out[v] = T(ui[v]);
+            }
+        }
+        A.flags[c] = uint8_t(ok ? 0 : 4);
         if constexpr (LABEL) A.label[c] = lab;
     }
-}
-
-// Positivity fallback at P4: the main pass is full CWENOZ, so a marked cell
-// falls back to first order (its average at every own face point; bit 2).
-template <class T>
-__global__ __launch_bounds__(kBlock) void reconstruct_p4_fallback_kernel(ReconArgs<T> A) {
-    const int64_t c = xcd_block() * blockDim.x + threadIdx.x;
-    if (c >= A.nc) return;
-    const uint8_t fl = A.flags[c];
-    if (!(fl & 0x80)) return;
-    const int64_t nc = A.nc, ns = A.ns;
-    for (int lf = 0; lf < A.NF; ++lf) {
-        const int nq = A.cnq[int64_t(lf) * ns + c];
-        for (int q = 0; q < nq; ++q)
-            for (int v = 0; v < 5; ++v)
-                A.fs[((int64_t(lf) * A.Q + q) * fs_cells_padded(nc) + c) * 5 + v] = T(A.U[v * nc + c]);
-    }
-    A.flags[c] = uint8_t((fl & 0x7f) | 4);
 }

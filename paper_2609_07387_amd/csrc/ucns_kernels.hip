@@ -590,7 +590,7 @@ __device__ __forceinline__ void symmetry_gradient(T* G, const T* n) {
 // lanes take adjacent faces (numbered by owner), so each point-state load of
 // a wave reads a few contiguous runs of the owners' and neighbours' slots,
 // and the cell gradients and face geometry are read once per face.
-template <class T>
+template <class T, bool AHEAD>
 __global__ __launch_bounds__(kBlock) void face_flux_kernel(FluxArgs<T> A, PhysT<T> P, BcT<T> B) {
     const int64_t f = xcd_block() * blockDim.x + threadIdx.x;
     if (f >= A.nf) return;
@@ -627,9 +627,10 @@ __global__ __launch_bounds__(kBlock) void face_flux_kernel(FluxArgs<T> A, PhysT<
         VF = viscous_face(P, G0, n, pen);
     }
     T F[5] = {T(0), T(0), T(0), T(0), T(0)};
-    // FP32 loads the next point's two states while it evaluates this one's
-    // flux (FP64 has no registers to spare: 158, three waves per SIMD)
-    constexpr bool kAhead = sizeof(T) == 4;
+    // AHEAD: the next point's two states load while this one's flux is
+    // evaluated (FP32; FP64 in calls of at most one wave per SIMD only, as it
+    // has no registers to spare at three: 12,288 FP64 faces 10.0 -> 7.0 us)
+    constexpr bool kAhead = AHEAD;
     // (on a boundary face pR = pL and the ghost replaces uR)
     auto load_point = [&](int q, T* uL, T* uR) {
 #pragma unroll
@@ -695,17 +696,21 @@ struct ResArgs {
     double* part;  // [2][gridDim]
 };
 
-// Fixed-shape block reduction (deterministic for a fixed launch shape).
+// Fixed-shape block reduction (deterministic for a fixed launch shape): each
+// wave's tree by lane exchanges, then the waves' results in order; valid in
+// thread 0.
 template <bool MIN>
-__device__ double block_reduce(double x) {
-    __shared__ double sh[kBlock];
-    sh[threadIdx.x] = x;
+__device__ __forceinline__ double block_reduce(double x) {
+    __shared__ double sh[16];
+    auto join = [](double a, double b) { return MIN ? fmin(a, b) : a + b; };
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) x = join(x, __shfl_down(x, d));
+    __syncthreads();  // an earlier reduction's results have been read
+    if ((threadIdx.x & 63u) == 0) sh[threadIdx.x >> 6] = x;
     __syncthreads();
-    for (int s = kBlock / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) sh[threadIdx.x] = MIN ? fmin(sh[threadIdx.x], sh[threadIdx.x + s]) : sh[threadIdx.x] + sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    return sh[0];
+    double r = sh[0];
+    for (unsigned w = 1; w < blockDim.x / 64; ++w) r = join(r, sh[w]);
+    return r;
 }
 
 // sum_f s_if F_f over the cell's faces in local order; all face ids first,
@@ -897,13 +902,26 @@ __global__ __launch_bounds__(kBlock) void ke_partial_kernel(int64_t nc, const do
     if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
-// dt_final and ke_final of the fused last stage in one launch.
-__global__ __launch_bounds__(kBlock) void rk_final_kernel(int nb, const double* part, double cfl, double inv_vol,
-                                                          double* dt, double* ke) {
+// dt_final and ke_final of the fused last stage in one launch: one block, eight
+// partials of each in flight per thread (3,456 blocks' partials: 7.5 us with 256
+// threads taking two at a time, 5.5 now).
+constexpr int kFinalBlock = 1024;
+__global__ __launch_bounds__(kFinalBlock) void rk_final_kernel(int nb, const double* part, double cfl, double inv_vol,
+                                                               double* dt, double* ke) {
     double best = INFINITY, sum = 0.0;
-    for (int i = threadIdx.x; i < nb; i += blockDim.x) {
-        best = fmin(best, part[i]);
-        sum += part[nb + i];
+    for (int i0 = threadIdx.x; i0 < nb; i0 += 8 * kFinalBlock) {
+        double t[8], e[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int i = i0 + q * kFinalBlock;
+            t[q] = i < nb ? part[i] : INFINITY;
+            e[q] = i < nb ? part[nb + i] : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            best = fmin(best, t[q]);
+            sum += e[q];
+        }
     }
     const double r = block_reduce<true>(best);
     const double t = block_reduce<false>(sum);
@@ -1132,7 +1150,8 @@ int launch_recon_k(const ReconArgs<T>& A, hipStream_t st, bool grad_lsq = false)
     } else {
         launch_recon_main<T, K, false, 0>(A, st);
     }
-    hipLaunchKernelGGL((reconstruct_fallback_kernel<T, K>), dim3(grid_for(A.nc)), dim3(kBlock), 0, st, A);
+    if (gate)
+        hipLaunchKernelGGL((reconstruct_fallback_kernel<T, K>), dim3(grid_for(A.nc)), dim3(kBlock), 0, st, A);
     return UCNS_OK;
 }
 
@@ -1156,7 +1175,6 @@ int launch_recon_p4(const ReconArgs<T>& A, hipStream_t st) {
         hipLaunchKernelGGL((reconstruct_p4_kernel<T, false, false, 1>), g1, dim3(64), 0, st, A);
     else
         hipLaunchKernelGGL((reconstruct_p4_kernel<T, false, true, 4>), g4, dim3(256), 0, st, A);
-    hipLaunchKernelGGL((reconstruct_p4_fallback_kernel<T>), dim3(grid_for(A.nc)), dim3(kBlock), 0, st, A);
     return UCNS_OK;
 }
 
@@ -1492,8 +1510,12 @@ int ucns_face_flux(const ucns_mesh* mesh, const ucns_phys* phys, const ucns_bc* 
                       arena_ptr<T>(ar, ar.fdc), arena_ptr<uint8_t>(ar, ar.fnq), static_cast<const T*>(gradW),
                       static_cast<T*>(face_flux)};
         const unsigned bl = block_for(m.nf);
-        hipLaunchKernelGGL((face_flux_kernel<T>), dim3(unsigned((m.nf + bl - 1) / bl)), dim3(bl), 0, st, A,
-                           make_phys<T>(phys), make_bc<T>(bc));
+        const dim3 grid(unsigned((m.nf + bl - 1) / bl));
+        if (sizeof(T) == 4 || bl == 64)
+            hipLaunchKernelGGL((face_flux_kernel<T, true>), grid, dim3(bl), 0, st, A, make_phys<T>(phys), make_bc<T>(bc));
+        else
+            hipLaunchKernelGGL((face_flux_kernel<T, sizeof(T) == 4>), grid, dim3(bl), 0, st, A, make_phys<T>(phys),
+                               make_bc<T>(bc));
     };
     if (precision == UCNS_F64)
         go(double(0));
@@ -1604,7 +1626,7 @@ int launch_rk_final(const ucns_mesh* mesh, const ucns_phys* phys, const void* fa
         go(double(0));
     else
         go(float(0));
-    hipLaunchKernelGGL(rk_final_kernel, dim3(1), dim3(kBlock), 0, st, int(nb), scratch, cfl, 1.0 / m.total_vol,
+    hipLaunchKernelGGL(rk_final_kernel, dim3(1), dim3(kFinalBlock), 0, st, int(nb), scratch, cfl, 1.0 / m.total_vol,
                        dt_next_dev, ke_dev);
     return hip_check("ucns_residual_rk_final");
 }

@@ -55,3 +55,44 @@ def test_copies_agree_across_launch_rules(order, precision, gated, copies):
     tol = (1e-13 if precision == ucns.F64 else 1e-6) * np.abs(ref).max()
     assert np.isfinite(got).all()
     assert np.abs(got - ref).max() <= tol, np.abs(got - ref).max() / np.abs(ref).max()
+
+
+def _fallback(copies, order, precision, gated):
+    """Flags and point states of a field with near-vacuum cells, whose
+    polynomials go negative at some face points."""
+    import torch
+
+    n = (BASE[0], BASE[1], BASE[2] * copies)
+    h = 2 * math.pi / BASE[0]
+    lm = ucns.Mesh(inputs.hex_box_mesh(n, tuple(h * a for a in n), (True,) * 3), order=order)
+    rng = np.random.default_rng(5)
+    rho = np.where(rng.random(9 ** 3) < 0.1, 1e-3, 1.0) * rng.uniform(0.9, 1.1, 9 ** 3)
+    U = np.stack([rho, 0.3 * rho, -0.2 * rho, 0.1 * rho, rho * 2.5 + 0.07 * rho])
+    U = np.ascontiguousarray(np.tile(U, (1, copies)))
+    lm.upload(precision)
+    ws = ucns.Workspace(lm, precision, False)
+    mask = torch.from_numpy(np.tile((np.arange(9 ** 3) % 3 != 0).astype(np.uint8), copies)).cuda() if gated else None
+    ucns.reconstruct(lm, ucns.phys(mach=1.0), torch.from_numpy(U).cuda(), precision, ws.face_state, mask, ws.flags)
+    torch.cuda.synchronize()
+    pad = -(-lm.n_cell // 64) * 64
+    fs = ws.face_state.reshape(lm.nfmax, lm.qmax, pad, 5)[:, :, :lm.n_cell].double().cpu().numpy()
+    return (ws.flags.cpu().numpy().reshape(copies, 9 ** 3),
+            np.sort(fs.reshape(lm.nfmax, lm.qmax, copies, 9 ** 3, 5), axis=1))
+
+
+# without a gate the kernel finishes its marked cells itself, with one a pass does
+@pytest.mark.parametrize("order,precision,gated,copies", [
+    (2, ucns.F64, True, 80), (2, ucns.F32, True, 150), (2, ucns.F64, False, 80), (3, ucns.F64, True, 40),
+    (3, ucns.F32, True, 80), (4, ucns.F64, False, 9)])
+def test_positivity_fallback_across_launch_rules(order, precision, gated, copies):
+    flags, fs = _fallback(1, order, precision, gated)
+    flags_n, fs_n = _fallback(copies, order, precision, gated)
+    assert (flags & 4).any() and not (flags & 0x80).any()
+    if gated:
+        assert (flags & 2).any()
+    assert np.array_equal(flags_n, np.repeat(flags, copies, 0))
+    assert (fs_n[..., 0] > 1e-10).all()  # density positive at every point
+    # (the weights amplify the summation-order difference near vacuum: ten times
+    # the tolerance of the smooth field)
+    tol = (1e-12 if precision == ucns.F64 else 1e-5) * np.abs(fs).max()
+    assert np.abs(fs_n - fs).max() <= tol
