@@ -1151,7 +1151,7 @@ int launch_recon_k(const ReconArgs<T>& A, hipStream_t st, bool grad_lsq = false)
         launch_recon_main<T, K, false, 0>(A, st);
     }
     if (gate)
-        hipLaunchKernelGGL((reconstruct_fallback_kernel<T, K>), dim3(grid_for(A.nc)), dim3(kBlock), 0, st, A);
+        hipLaunchKernelGGL((reconstruct_fallback_kernel<T, K>), dim3(unsigned((A.nc + 63) / 64)), dim3(64), 0, st, A);
     return UCNS_OK;
 }
 
