@@ -58,7 +58,10 @@ def recon_bytes_per_cell(lm, precision, linear=False, gate=False, grad=False):
     the call also forms the Green-Gauss gradients (the face-neighbour ids,
     unless the gate has read them, each face slot's three weights, the twelve
     gradient values written).  At order 4 the call also stages the state
-    cell-interleaved (40 bytes read, 64 written per cell)."""
+    cell-interleaved (40 bytes read, 64 written per cell).  The model counts the
+    scheme's stored operators, the indicator matrix among them; the FP64 P2 and
+    the P3 kernels form their indicators from 1 or 16 values per cell and the
+    basis means instead of its 45 or 190 entries, so they move less."""
     t = 8 if precision == 0 else 4
     K, MC, MD, ND, NF, Q = lm.K, lm.mc_pad, max(1, lm.md_pad), max(1, lm.nd_max), lm.nfmax, lm.qmax
     KD = getattr(lm, "kd", 3)  # terms of a directional polynomial (3 linear, 9 quadratic at P4)
