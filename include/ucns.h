@@ -243,7 +243,7 @@ int ucns_dt(const ucns_mesh* mesh, const ucns_phys* phys, const double* U, doubl
  * weights, blend, and the polynomial values at the cell's face quadrature
  * points written to face_state.  Positivity of density and pressure at every
  * point is enforced with the fallback gated-linear -> full CWENOZ -> first
- * order, run as a second pass over the cells that need it; flags[c]
+ * order (with a gate, a second pass over the cells that need it); flags[c]
  * (device [n_cell], required) records bit0 linear taken, bit1 CWENOZ
  * fallback, bit2 first-order fallback.  label (device float [n_cell],
  * may be NULL; only without a gate) receives max over variables and stencils

@@ -93,10 +93,9 @@ __device__ __forceinline__ void p4_jumps(double uh, double u4, const double* ui,
     bv[4] = T(u4 - ui[4]);
 }
 
-// The member stream of a list of stencils: member q (q = 0 .. n-1) has its
-// id at row q of `sten` and its KR operator rows at rows q KR .. of `op`
-// (the wave's tile, [row][16 cells]); the lane loads the rows at its byte
-// offsets off[].
+// The member stream of a stencil: members q = 0 .. n-1, their ids in `sten` (one
+// run of 64 per four members) and their KR x 16 operator values each in `op`, of
+// which the lane loads those at its byte offsets off[].
 // body(q, bv, b) receives the member's five jumps and the lane's operator
 // values.  Loads run ahead of the arithmetic in 8-member trips with
 // compile-time register slots (no register is copied while its load is in
@@ -260,8 +259,7 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
     const int64_t nc = A.nc, ns = A.ns;
     const int lane = int(threadIdx.x & 63u);
     const int slot = lane >> 2, h = lane & 3;
-    // the wave's tile of 16 cells; the mesh arrays are [tile][row][16 cells],
-    // so that each load of four rows is one contiguous run
+    // the wave's tile of 16 cells (mesh arrays by tiles in lane order, kP4Tile)
     const int64_t tile = xcd_block() * WB + __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const int64_t c0 = tile * kP4Cells;
     const bool valid = c0 + slot < nc;
@@ -290,8 +288,7 @@ void reconstruct_p4_kernel(ReconArgs<T> A) {
 #pragma unroll
     for (int i = 0; i < NT; ++i) toff[i] = uint32_t(p4_pos<K>(min(4 * i + h, K - 1), slot)) * uint32_t(sizeof(T));
 
-    // (ii) central coefficients; member m's id at sten_c[m][c], its K
-    // operator rows at Bc[m][k][c].
+    // (ii) central coefficients
     T a[5][NT];
 #pragma unroll
     for (int v = 0; v < 5; ++v)
