@@ -886,6 +886,11 @@ __device__ __forceinline__ void dir_blend_wave(const ReconArgs<T>& A, uint64_t t
         todo &= todo - 1;
         const int64_t cL = __builtin_amdgcn_readlane(int(c), L);
         const int ndL = __builtin_amdgcn_readlane(nd, L);
+        // with every lane active: under the condition below lane L may be off,
+        // and a register copy made there leaves its value behind
+        double uL[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) uL[v] = lane_read(ui[v], L);
         T x[3][5];
 #pragma unroll
         for (int k = 0; k < 3; ++k)
@@ -898,7 +903,7 @@ __device__ __forceinline__ void dir_blend_wave(const ReconArgs<T>& A, uint64_t t
             for (int k = 0; k < 3; ++k) b[k] = A.Bd[(int64_t(lane) * 3 + k) * ns + cL];
 #pragma unroll
             for (int v = 0; v < 5; ++v) {
-                const T bv = T(A.U[v * nc + j] - lane_read(ui[v], L));
+                const T bv = T(A.U[v * nc + j] - uL[v]);
 #pragma unroll
                 for (int k = 0; k < 3; ++k) x[k][v] = b[k] * bv;
             }
