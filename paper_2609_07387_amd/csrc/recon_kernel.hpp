@@ -637,6 +637,15 @@ __device__ __forceinline__ void blend_init(const ReconArgs<T>& A, int64_t c, int
     B.th = A.th[c];
 }
 
+// Indicator th (x^2 + y^2 + z^2) of a linear polynomial, fused by hand: left to
+// the compiler, the sum is contracted in one way or another from kernel to
+// kernel, and the nonlinear weights turn the difference into one rounding of the
+// FP32 point states and up to 5e-8 of a run's FP64 state.
+template <class T>
+__device__ __forceinline__ T linear_si(T th, T x, T y, T z) {
+    return fmax(fma(z * th, z, fma(y, th * y, x * (th * x))), T(0));
+}
+
 // One directional stencil with linear coefficients as: its indicator and its
 // share of the blend.
 template <class T>
@@ -644,7 +653,7 @@ __device__ __forceinline__ void blend_add(const ReconArgs<T>& A, Blend<T>& B, co
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
         const T x = as[0][v], y = as[1][v], z = as[2][v];
-        const T SIs = fmax(x * (B.th * x) + y * (B.th * y) + z * B.th * z, T(0));
+        const T SIs = linear_si(B.th, x, y, z);
         B.tsum[v] += fabs(B.SI1[v] - SIs);
         const T r = T(1) / (A.eps + SIs);
         B.Lam[v] += B.lam_s * r;
@@ -1059,7 +1068,7 @@ __device__ __forceinline__ void dir_blend_stencils(const ReconArgs<float>& A, ui
 #pragma unroll
             for (int v = 0; v < 5; ++v) {
                 const T x = as[0][v], y = as[1][v], z = as[2][v];
-                const T SIs = fmax(x * (th * x) + y * (th * y) + z * th * z, T(0));
+                const T SIs = linear_si(th, y, x, z);  // (in this order: the rounding this path has always had)
                 ts[v] = fabs(SI1p[v] - SIs);
                 const T r = T(1) / (A.eps + SIs);
                 lm[v] = lam_s * r;

@@ -74,3 +74,16 @@ def test_few_troubled_cells_take_the_ungated_values(mesh, order, precision):
             assert np.array_equal(flags[t], rflags[t])
             worst = max(worst, (np.abs(fs - ref)[:, t] / scale).max())
     assert worst <= tol, worst
+
+
+@pytest.mark.parametrize("precision", [ucns.F64, ucns.F32])
+@pytest.mark.parametrize("mesh", ["hex", "tet", "mixed"])
+def test_all_troubled_is_the_ungated_call_bitwise(mesh, precision):
+    """A mask without a smooth cell has every wave take the lane-per-cell path
+    (no wave of these meshes holds fewer than 40 cells), the ungated call's own:
+    the same operations in the same order, so the same bits."""
+    lm, U, run = _setup(mesh, 2, precision)
+    ref, rflags = run(None)
+    fs, flags = run(np.zeros(lm.n_cell, np.uint8))
+    assert np.array_equal(flags, rflags)
+    assert np.array_equal(fs, ref), np.abs(fs - ref).max()
