@@ -371,7 +371,11 @@ __device__ __forceinline__ void si_matrix(const ReconArgs<T>& A, int64_t c, cons
 // multiply-adds.  The calls are bound by HBM, so the bytes are what counts:
 // FP64 64^3 hex P2 call 332 -> 312 us, 196,608 P3 tets FP64 443 -> 404 us,
 // 44,574 FP32 65.4 -> 61.9 us.
-template <class T, int K>
+//
+// LABEL: as the matrix form, whose zero entries meet every coefficient, the
+// indicator of a polynomial with an infinite coefficient is NaN, and so 0 (the
+// point states don't need it: such a cell is first order either way).
+template <class T, int K, bool LABEL = false>
 __device__ __forceinline__ void si_opt(const ReconArgs<T>& A, int64_t c, const T a[K][5], T SI1[5]) {
     static_assert(K == 9 || K == 19);
     if constexpr (K == 9 && sizeof(T) == 4) {
@@ -453,6 +457,12 @@ __device__ __forceinline__ void si_opt(const ReconArgs<T>& A, int64_t c, const T
                 S[2] += q * q;
             });
         SI1[v] = th * (S[0] + th * (S[1] + th * S[2]));
+        if constexpr (LABEL) {
+            T nan = T(0);
+#pragma unroll
+            for (int k = 0; k < K; ++k) nan += T(0) * a[k][v];
+            SI1[v] += nan;
+        }
         SI1[v] = fmax(SI1[v], T(0));
     }
 }
@@ -619,11 +629,11 @@ struct Blend {
     T th;  // the linear block of O is th times the identity
 };
 
-template <class T, int K>
+template <class T, int K, bool LABEL = false>
 __device__ __forceinline__ void blend_init(const ReconArgs<T>& A, int64_t c, int nd, const T a[K][5], Blend<T>& B) {
     B.lam_s = T(1) / (A.lam_c + T(nd));
     B.lam_1 = A.lam_c * B.lam_s;
-    si_opt<T, K>(A, c, a, B.SI1);
+    si_opt<T, K, LABEL>(A, c, a, B.SI1);
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
         B.tsum[v] = T(0);
@@ -641,19 +651,21 @@ __device__ __forceinline__ void blend_init(const ReconArgs<T>& A, int64_t c, int
 // the compiler, the sum is contracted in one way or another from kernel to
 // kernel, and the nonlinear weights turn the difference into one rounding of the
 // FP32 point states and up to 5e-8 of a run's FP64 state.
-template <class T>
+template <class T, bool LABEL = false>
 __device__ __forceinline__ T linear_si(T th, T x, T y, T z) {
-    return fmax(fma(z * th, z, fma(y, th * y, x * (th * x))), T(0));
+    T s = fma(z * th, z, fma(y, th * y, x * (th * x)));
+    if constexpr (LABEL) s += T(0) * y + T(0) * z;  // (si_opt)
+    return fmax(s, T(0));
 }
 
 // One directional stencil with linear coefficients as: its indicator and its
 // share of the blend.
-template <class T>
+template <class T, bool LABEL = false>
 __device__ __forceinline__ void blend_add(const ReconArgs<T>& A, Blend<T>& B, const T as[3][5]) {
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
         const T x = as[0][v], y = as[1][v], z = as[2][v];
-        const T SIs = linear_si(B.th, x, y, z);
+        const T SIs = linear_si<T, LABEL>(B.th, x, y, z);
         B.tsum[v] += fabs(B.SI1[v] - SIs);
         const T r = T(1) / (A.eps + SIs);
         B.Lam[v] += B.lam_s * r;
@@ -700,7 +712,7 @@ __device__ __forceinline__ void dir_blend_lane(const ReconArgs<T>& A, int64_t c,
                                                T a[K][5]) {
     const int64_t nc = A.nc, ns = A.ns;
     Blend<T> B;
-    blend_init<T, K>(A, c, nd, a, B);
+    blend_init<T, K, LABEL>(A, c, nd, a, B);
     // all directional members as one pipelined stream t = s * MD + m over
     // every stencil slot (a wave-uniform count; the slots past the cell's
     // nd hold zero operators and are not counted); the id of member t at
@@ -759,7 +771,7 @@ __device__ __forceinline__ void dir_blend_lane(const ReconArgs<T>& A, int64_t c,
                         for (int v = 0; v < 5; ++v) as[k][v] += b[SL][k] * bv[v];
                     if (m + 1 == MD) {
                         // stencil s complete
-                        if (s < nd) blend_add<T>(A, B, as);
+                        if (s < nd) blend_add<T, LABEL>(A, B, as);
 #pragma unroll
                         for (int k = 0; k < 3; ++k)
 #pragma unroll
@@ -818,7 +830,7 @@ __device__ __forceinline__ void dir_blend_lane(const ReconArgs<T>& A, int64_t c,
                 for (int v = 0; v < 5; ++v) as[k][v] += b[0][k] * bv[v];
             if (m + 1 == MD) {
                 // stencil s complete
-                if (s < nd) blend_add<T>(A, B, as);
+                if (s < nd) blend_add<T, LABEL>(A, B, as);
 #pragma unroll
                 for (int k = 0; k < 3; ++k)
 #pragma unroll
