@@ -1043,11 +1043,16 @@ ReconArgs<T> make_recon_args(const Mesh& m, const Arena& ar, double gm1, const d
     // the arena's one scratch region (written by the P4 reconstruction call)
     A.ustage = ar.ustage ? reinterpret_cast<double*>(static_cast<unsigned char*>(ar.dev) + ar.ustage) : nullptr;
     A.fs = static_cast<T*>(fs);
-    // point states that fit the Infinity Cache are still there when the flux
-    // kernel reads them (64^3 gated FP32 step, 126 MB: 573 us, 582 us with
-    // non-temporal stores); larger ones only push other data out (284,000
-    // mixed FP64 cells, 273 MB: 441 us, 432 us non-temporally)
-    A.fs_nt = int64_t(sizeof(T)) * 5 * m.nfmax * m.qmax * fs_cells_padded(m.nc) > kInfinityCache;
+    // Point states that fit the Infinity Cache beside U, the gradients and the
+    // fluxes are still there when the flux kernel reads them; larger ones only
+    // push other data out.  Plain / non-temporal stores, by their size: 64^3 gated
+    // FP32 step, 126 MB, 580 / 590 us; 52^3 FP64 step, 135 MB, 711 / 735;
+    // 357,000 P2 FP64 tetrahedra, 171 MB, 1,383 / 1,384; 72^3 FP32 step, 179 MB,
+    // 1,072 / 1,088; then 58^3 FP64 step, 187 MB, 863 / 858; 75^3 FP32, 202 MB,
+    // 1,255 / 1,241; 64^3 FP64, 252 MB, 1,203 / 1,167; 445,000 P3 FP64
+    // tetrahedra, 213 MB, right-hand side 967 / 896; 257,000 mixed FP64 cells, 247 MB,
+    // right-hand side 370 / 358.
+    A.fs_nt = int64_t(sizeof(T)) * 5 * m.nfmax * m.qmax * fs_cells_padded(m.nc) > kInfinityCache / 16 * 11;
     A.flags = flags;
     A.label = label;
     A.lam_c = T(m.lambda_c);
