@@ -11,7 +11,10 @@ import math
 import numpy as np
 import pytest
 
+import oracle
 from paper_2609_07387_amd import inputs, ucns
+
+from parity_helpers import as_oracle_phys, face_maps, face_major
 
 pytestmark = pytest.mark.gpu
 
@@ -109,3 +112,52 @@ def test_both_sides_of_each_rule(order, precision, gated, copies, sides):
         for k in np.nonzero(first.any(axis=1))[0]:
             assert np.array_equal(fs[:, :, k, first[k]], np.broadcast_to(avg[first[k]], fs[:, :, k, first[k]].shape))
     assert first.any() and not (flags & 0x80).any()
+
+
+@pytest.mark.parametrize("precision", [ucns.F64, ucns.F32])
+@pytest.mark.parametrize("gated", [False, True])
+@pytest.mark.parametrize("mesh,order", [("tet", 2), ("tet", 3), ("mixed", 2)])
+def test_positivity_fallback_on_tets_and_mixed_cells(mesh, order, gated, precision):
+    """The fallback on triangles (three points a face, staged three at a time at
+    P3), on cells with fewer faces than slots and, with a gate on the mixed mesh,
+    in waves whose cells have stencils of several sizes (the fallback pass walks
+    the largest of its marked cells' own).  FP64: flags and point states as the
+    oracle's (1e-9 of the largest value: condition numbers up to 2e4 times 1e-14,
+    amplified near vacuum).  Both precisions: a first-order cell holds its average
+    at its own points exactly, any other is positive there."""
+    import torch
+
+    if mesh == "tet":
+        m = inputs.kuhn_tet_mesh((5, 5, 4), tuple(2 * math.pi * a / 8 for a in (5, 5, 4)), (True,) * 3)
+    else:
+        m = inputs.mixed_bl_mesh((9, 5, 6), (2.25, 1.0, 0.75), (2, 2), 2, 1.2, 0.15, 0.05)
+    lm, om = ucns.Mesh(m, order=order), oracle.OracleMesh(m, order=order)
+    if mesh == "mixed":
+        assert om.mc_min < om.mc_max and lm.nfmax == 6
+    n = m.n_cell
+    rng = np.random.default_rng(7)
+    rho = np.where(rng.random(n) < 0.1, 1e-3, 1.0) * rng.uniform(0.9, 1.1, n)
+    U = np.stack([rho, 0.3 * rho, -0.2 * rho, 0.1 * rho, 2.57 * rho])
+    mask = (rng.random(n) < 0.7).astype(np.uint8) if gated else None
+    ph = ucns.phys(flux="hllc", mach=1.0)
+    lm.upload(precision)
+    ws = ucns.Workspace(lm, precision, False)
+    ucns.reconstruct(lm, ph, torch.from_numpy(U).cuda(), precision, ws.face_state,
+                     None if mask is None else torch.from_numpy(mask).cuda(), ws.flags)
+    torch.cuda.synchronize()
+    flags = ws.flags.cpu().numpy()
+    ofs, oflags, _ = om.reconstruct(U, as_oracle_phys(ph), mask, with_flags=True)
+    fl, fo, sl = face_maps(lm, om)
+    a, b = face_major(lm, ws.face_state.double().cpu().numpy())[fl, sl, :lm.qmax], ofs[fo, sl, :lm.qmax]
+    own = np.nonzero(om.cell_faces()[0] >= 0)[0]  # the cell of each (face, side) pair
+    valid = ~np.isnan(b[..., 0])
+    assert (flags & 4).any() and (not gated or (flags & 2).any()) and not (flags & 0x80).any()
+    if precision == ucns.F64:
+        assert np.array_equal(flags, oflags)
+        assert np.abs(a - b)[valid].max() <= 1e-9 * np.abs(U).max()
+    avg = (U if precision == ucns.F64 else U.astype(np.float32)).T.astype(np.float64)[own][:, None, :]
+    first = ((flags & 4) != 0)[own][:, None] & valid
+    assert np.array_equal(a[first], np.broadcast_to(avg, a.shape)[first])
+    rest = valid & ~first
+    rho_q, p_q = a[..., 0], 0.4 * (a[..., 4] - 0.5 * (a[..., 1:4] ** 2).sum(-1) / a[..., 0])
+    assert (rho_q[rest] > 0).all() and (p_q[rest] > 0).all()
