@@ -87,7 +87,7 @@ template <class T>
 struct ReconArgs {
     const double* U;
     int64_t nc;
-    int64_t ns;  // row stride of the mesh arrays ([row][ns])
+    int64_t ns;  // row stride of the padded mesh arrays ([row][ns]; P4's operators in tiles, kP4Tile)
     const int32_t* sten_c;
     const T* Bc;
     int MC;
@@ -100,9 +100,9 @@ struct ReconArgs {
     const T* O;    // upper triangle of the indicator matrix (reads_indicator_matrix)
     const T* th;   // V^(2/3) / h^2 per cell: the linear block of O is th times the identity
     const T* mom;  // P3: scaled moments of degree 4 [15][ns]
-    const T* xi;     // face points in each cell's scaled frame [lf][q][3][nc]
-    const T* pmean;  // cell means of the scaled monomials [K][nc]
-    const uint8_t* cnq;  // Gauss points of each face slot [lf][nc] (0: no face)
+    const T* xi;     // face points in each cell's scaled frame [lf][q][3][ns]
+    const T* pmean;  // cell means of the scaled monomials [K][ns]
+    const uint8_t* cnq;  // Gauss points of each face slot [lf][ns] (0: no face)
     int Q, NF;
     const uint8_t* gate;
     T* fs;
@@ -1099,26 +1099,28 @@ bool nt_streams(const ReconArgs<T>& A, int K) {
     return A.ns * (central + dir + t * 3 * A.NF * A.Q + slots) > kInfinityCache - (int64_t(6) << 20);
 }
 
-// Waves per block of a reconstruction call.  One-wave blocks spread over the
-// CUs when the call does not fill them (at most 2,048 waves, two per SIMD;
-// 4,096 FP64 cells 46 -> 35 us, 13,122 P3 FP32 tets 50 -> 39 us, 44,574 61 ->
-// 57 us, 27,000 P3 FP64 hexahedra 157 -> 136 us), and free their slots one by
-// one when the waves' work differs: gated (375,000 shocked tets 207 -> 196 us)
-// or with stencils of several sizes (mixed FP64 right-hand side 432 -> 421 us).
-// Four waves share a CU's cache when the call is large and even (64^3 FP64 302
-// against 307 us, 196,608 P3 FP64 tets 397 against 411 us).
-inline int recon_block_waves(int64_t waves, bool uneven) { return waves <= 2048 || uneven ? 1 : 4; }
+// Waves per block of a P2 or P3 reconstruction call (nt: nt_streams).  One-wave
+// blocks spread over the CUs when the call does not fill them (at most 2,048
+// waves, two per SIMD; 4,096 FP64 cells 46 -> 35 us, 13,122 P3 FP32 tets 50 -> 39
+// us, 44,574 61 -> 57 us, 27,000 P3 FP64 hexahedra 157 -> 136 us), and free their
+// slots one by one when the waves' work differs: gated (375,000 shocked tets 207
+// -> 196 us) or with stencils of several sizes (mixed FP64 right-hand side 432 ->
+// 421 us).  Streams that fit the Infinity Cache gain nothing from a shared CU
+// cache either, whatever the wave count (even FP32 P2 tetrahedra, one wave / four:
+// 2,058 waves 84 / 98 us, 2,287 103 / 122, 2,532 124 / 137).  Four waves share a
+// CU's cache when the call is large and even (64^3 FP64 302 against 307 us,
+// 196,608 P3 FP64 tets 397 against 411 us).
+inline int recon_block_waves(int64_t waves, bool uneven, bool nt) { return !nt || waves <= 2048 || uneven ? 1 : 4; }
 
 template <class T, int K, bool GATE, int GRAD>
 void launch_recon_main(const ReconArgs<T>& A, hipStream_t st) {
     const int64_t waves = (A.nc + 63) / 64;
     const bool nt = nt_streams(A, K);
-    // (streams that fit the Infinity Cache are those of small or gated calls)
-    const bool one = !nt || recon_block_waves(waves, GATE || A.MCmin < A.MC) == 1;
+    const int wb = recon_block_waves(waves, GATE || A.MCmin < A.MC, nt);  // (one with a gate or plain streams)
     const dim3 g1{unsigned(waves)}, g4{unsigned((waves + 3) / 4)};
     if (!nt)
         hipLaunchKernelGGL((reconstruct_kernel<T, K, false, GATE, GRAD, false, 1>), g1, dim3(64), 0, st, A);
-    else if (GATE || one)
+    else if (wb == 1)
         hipLaunchKernelGGL((reconstruct_kernel<T, K, false, GATE, GRAD, true, 1>), g1, dim3(64), 0, st, A);
     else if constexpr (!GATE)
         hipLaunchKernelGGL((reconstruct_kernel<T, K, false, GATE, GRAD, true, 4>), g4, dim3(256), 0, st, A);
@@ -1168,9 +1170,14 @@ int launch_recon_p4(const ReconArgs<T>& A, hipStream_t st) {
     if (recon_span_bytes(A.nc, int(sizeof(T)), kP4K, A.NF) > kMaxDescriptorBytes) return UCNS_EINVAL;
     hipLaunchKernelGGL(p4_stage_state_kernel, dim3(grid_for(A.nc)), dim3(kBlock), 0, st, A.U, A.nc, A.ustage);
     static_assert(kP4Cells == kP4Tile);
-    // (nt_streams' rule: 9,975 FP32 cells, 156 MB, 138 us plain and 161 marked;
-    // 64,000 FP64 cells 713 and 708 us; one-wave blocks for the calls that fit
-    // the cache, 1,485 FP32 cells 120 -> 114 us)
+    // Operators beyond the Infinity Cache (its 250 MB, the member ids and the rest
+    // not counted) are read non-temporally, by four-wave blocks; those that fit
+    // plainly, by one-wave blocks.  Plain / marked: 9,975 FP32 cells, 156 MB, 138 /
+    // 161 us; 64,000 FP64 cells 713 / 708.  One wave / four, plain: 990 FP32 cells
+    // 110 / 114 us, 8,820 124 / 124, 15,000 148 / 148, 2,197 FP64 cells 128 / 148,
+    // 7,600 165 / 186; marked: 29,791 FP64 cells 351 / 345, 64,000 694 / 690, but
+    // just past the limit 9,261 FP64 cells 165 / 181, 16,875 FP32 cells 163 / 182 and
+    // 39,304 253 / 270, where one would be the better side.
     const int64_t t = sizeof(T), waves = (A.nc + kP4Cells - 1) / kP4Cells;
     const bool nt = A.ns * t * (kP4K * A.MC + kP4KD * A.ND * A.MD) > kInfinityCache - (int64_t(6) << 20);
     const dim3 g1{unsigned(waves)}, g4{unsigned((waves + 3) / 4)};
