@@ -976,9 +976,10 @@ int build_mesh(const ucns_mesh_desc* d, const ucns_recon_opts* o, int n_threads,
 namespace ucns {
 
 // ------------------------------------------------------------------ packing
-// Device arena of one precision: every per-cell array is cell-fastest
-// ([entry][n_cell]) so that one thread per cell reads coalesced; stencil
-// members are listed in ascending cell id (operator columns permuted alike)
+// Device arena of one precision: per-cell arrays are cell-fastest ([entry][ns],
+// rows padded to row_stride; th, hb, ncen, ndir, vol and hdt, one value a cell,
+// [n_cell]; P4's operators in tiles, kP4Tile) so that one thread per cell reads
+// coalesced; stencil members are listed in ascending cell id (operator columns permuted alike)
 // so that neighbouring threads gather from nearby cells.
 namespace {
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -1068,7 +1069,7 @@ void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
         std::sort(perm.begin(), perm.begin() + n, [&](int x, int y) { return ids[x] < ids[y]; });
         for (int j = 0; j < MC; ++j) {
             sten_c[at_id(0, j, 1, MC, c)] = j < n ? int32_t(ids[perm[j]]) : int32_t(c);
-            for (int k = 0; k < K; ++k)  // member-major rows: (j, k) at (j K + k) nc
+            for (int k = 0; k < K; ++k)  // member-major
                 Bc[at_op(j, MC, k, K, c)] = j < n ? T(m.Bc[(size_t(c) * K + k) * MC + perm[j]]) : T(0);
         }
         ndir[c] = uint8_t(m.ndir[c]);
@@ -1079,7 +1080,7 @@ void fill_arena(const Mesh& m, const Arena& a, unsigned char* base) {
             std::sort(perm.begin(), perm.begin() + nd, [&](int x, int y) { return dids[x] < dids[y]; });
             for (int j = 0; j < MD; ++j) {
                 sten_d[at_id(s, j, ND, MD, c)] = j < nd ? int32_t(dids[perm[j]]) : int32_t(c);
-                for (int k = 0; k < KD; ++k)  // member-major rows: (s, j, k) at ((s MD + j) kd + k) nc
+                for (int k = 0; k < KD; ++k)  // member-major
                     Bd[at_op(s * MD + j, ND * MD, k, KD, c)] =
                         j < nd ? T(m.Bd[((size_t(c) * m.nd_max + s) * KD + k) * m.md_pad + perm[j]]) : T(0);
             }

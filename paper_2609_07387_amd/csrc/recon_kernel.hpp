@@ -335,7 +335,9 @@ constexpr int mono_at(int i, int j, int k) { return i + j + k == 0 ? -1 : kMono.
 
 // SI_1 = a^T O a with O stored as its upper triangle (FP32 P2: the formula
 // below rounds the indicators differently, and through the nonlinear weights
-// a run's FP64 state by more than 1e-9 of itself, for 2 % of a call's time).
+// a run's FP64 state by more than 1e-9 of itself.  The matrix costs 180 of 3,080
+// bytes an ungated cell and 1 to 3 % of a call: 64^3 reconstruction 184.9 against
+// 180.2 us, 61 x 47 x 39 right-hand side 112.7 against 111.2).
 template <class T, int K>
 __device__ __forceinline__ void si_matrix(const ReconArgs<T>& A, int64_t c, const T a[K][5], T SI1[5]) {
     const int64_t ns = A.ns;

@@ -47,12 +47,7 @@ inline uint64_t recon_span_bytes(int64_t nc, int elem_bytes, int K, int NF) {
                               uint64_t(5) * uint64_t(elem_bytes) * uint64_t(fs_cells_padded(nc)));
 }
 constexpr uint64_t kMaxDescriptorBytes = 0xffffffffull;
-// Row stride of the per-cell mesh arrays ([row][stride]): the cell count
-// padded to whole 64-cell tiles, so that a wave's run of a row starts on a
-// cache line (an odd cell count would have it touch three 128-byte lines where
-// two hold it, and the streamed lines shared with the next wave be fetched
-// twice); the plain count where the padding would push a descriptor past its
-// limit.
+
 // P4: a wave takes a tile of 16 cells with a quad of lanes per cell, lane
 // 4 slot + h owning the basis terms 4 i + h.  Its arrays are stored tile by tile
 // in the order the wave's lanes read them, so that each load is one contiguous
@@ -78,12 +73,18 @@ constexpr int kP4ORuns = 4 * 45;
 constexpr int p4_o_run(int X, int i, int j) {
     return j < 3 ? X * 6 + j * (j + 1) / 2 + i : 24 + X * 39 + (j * (j + 1) / 2 - 6) + i;
 }
+
+// Row stride of the per-cell mesh arrays ([row][stride]): the cell count
+// padded to whole 64-cell tiles, so that a wave's run of a row starts on a
+// cache line (an odd cell count would have it touch three 128-byte lines where
+// two hold it, and the streamed lines shared with the next wave be fetched
+// twice); the plain count where the padding would push a descriptor past its
+// limit.
 inline int64_t row_stride(int64_t nc, int K) {
     const int64_t padded = fs_cells_padded(nc);
     if (K == kMaxK) return padded;  // whole tiles
     return uint64_t(std::max(K, 5)) * 8u * uint64_t(padded) <= kMaxDescriptorBytes ? padded : nc;
 }
-
 
 // Offsets (bytes) of every array inside one precision's device arena (per-cell
 // arrays [row][ns], ns = Mesh::ns; P4's operators in tiles, kP4Tile).
@@ -93,13 +94,13 @@ struct Arena {
     // smoothness indicators: V^(2/3) / h^2 per cell and the scaled moments of degree 4 (P3); where
     // reads_indicator_matrix, the matrix O
     size_t th = 0, mom = 0;
-    size_t cnq = 0;  // [nfmax][nc] Gauss points of each of a cell's face slots (0: no face)
+    size_t cnq = 0;  // [nfmax][ns] Gauss points of each of a cell's face slots (0: no face)
     size_t vol = 0, hdt = 0, fcell = 0, flf = 0, fnrm = 0, farea = 0, fw = 0, fdc = 0, fnq = 0;
-    // face neighbours ([nfmax][nc]; a boundary slot holds its face's negative tag, an absent one -1),
+    // face neighbours ([nfmax][ns]; a boundary slot holds its face's negative tag, an absent one -1),
     // their centroid offsets, basis scale, stencil size (gate features; fused gradients)
     size_t nbr = 0, ndc = 0, hb = 0, ncen = 0;
-    size_t glsq = 0;  // [nfmax][3][nc] least-squares gradient weights per face slot
-    size_t ggw = 0;   // [nfmax][3][nc] Green-Gauss weights per face slot: outward n |S| / (2 |V|)
+    size_t glsq = 0;  // [nfmax][3][ns] least-squares gradient weights per face slot
+    size_t ggw = 0;   // [nfmax][3][ns] Green-Gauss weights per face slot: outward n |S| / (2 |V|)
     size_t ustage = 0;  // P4 only: [nc][8] FP64, the state staged cell-interleaved by each reconstruction call
     void* dev = nullptr;  // caller-owned device pointer after upload
 };

@@ -6,10 +6,10 @@
 // cwenoz_weights, viscous_gradient_penalty, fv_update) with the per-stage
 // order of its time-step algorithm (Algorithm 1).
 //
-// Layout: per-cell operators and the point states each cell writes are
-// cell-fastest ([entry][n_cell]) so that one thread per cell streams them
-// coalesced; face geometry and face fluxes are face-major.  The
-// residual is a per-cell gather of single-valued face fluxes (no atomics),
+// Layout: per-cell operators are cell-fastest ([entry][cells padded to whole
+// 64-cell tiles]; in 16-cell tiles at P4) so that one thread per cell streams
+// them coalesced; point states are rows of 5-value cells, face geometry and face
+// fluxes face-major.  The residual is a per-cell gather of single-valued face fluxes (no atomics),
 // and the two reductions (dt, kinetic energy) use a fixed block count and a
 // fixed tree, so every result is bitwise reproducible.
 #include <hip/hip_runtime.h>
@@ -311,7 +311,7 @@ struct GradArgs {
     const T* fnrm;
     const T* farea;
     const double* vol;
-    const T* glsq;  // [nfmax][3][nc] least-squares weights per face slot
+    const T* glsq;  // [nfmax][3][ns] least-squares weights per face slot
     T* gradW;
 };
 
