@@ -45,7 +45,7 @@ TRAFFIC = {"fp32_gate": "traffic_reconstruct_fp32_gate_tgv64.md",
 METRIC = "cell-stage updates/s, P2 CWENO+HLLC: FP64 plain vs FP32+MLP gate; % HBM peak"
 
 
-def recon_bytes_per_cell(lm, precision, linear=False, gate=False, grad=False):
+def recon_bytes_per_cell(lm, precision, linear=False, gate=False, grad=False, read=False):
     """Algorithmic HBM bytes of one reconstruction of one cell: every operator
     value and index read once (the basis at a face point is recomputed from
     the point's 3 scaled coordinates and the cell's K basis means; one byte
@@ -58,15 +58,23 @@ def recon_bytes_per_cell(lm, precision, linear=False, gate=False, grad=False):
     the call also forms the Green-Gauss gradients (the face-neighbour ids,
     unless the gate has read them, each face slot's three weights, the twelve
     gradient values written).  At order 4 the call also stages the state
-    cell-interleaved (40 bytes read, 64 written per cell).  The model counts the
-    scheme's stored operators, the indicator matrix among them; the FP64 P2 and
-    the P3 kernels form their indicators from 1 or 16 values per cell and the
-    basis means instead of its 45 or 190 entries, so they move less."""
+    cell-interleaved (40 bytes read, 64 written per cell).
+
+    By default the indicators count as the scheme has them, the upper triangle
+    of the indicator matrix.  read: as the kernels read them.  FP64 P2 and P3
+    form them from one value per cell and the basis means (P3: 15 further
+    moments), FP32 P2 reads that value and the triangle, P4 its 595 entries in
+    180 runs of four lanes, 720 values with the padding, and member ids in
+    groups of four.  The reported rates count the bytes read."""
     t = 8 if precision == 0 else 4
     K, MC, MD, ND, NF, Q = lm.K, lm.mc_pad, max(1, lm.md_pad), max(1, lm.nd_max), lm.nfmax, lm.qmax
     KD = getattr(lm, "kd", 3)  # terms of a directional polynomial (3 linear, 9 quadratic at P4)
-    ops = K * MC + NF * Q * 3 + K + (0 if linear else K * (K + 1) // 2 + ND * KD * MD)
-    idx = MC + (0 if linear else ND * MD)
+    ind = K * (K + 1) // 2
+    if read:
+        ind = 720 if K == 34 else 16 if K == 19 else 1 if t == 8 else ind + 1
+    ops = K * MC + NF * Q * 3 + K + (0 if linear else ind + ND * KD * MD)
+    group = 4 if read and K == 34 else 1  # member ids per group
+    idx = -(-MC // group) * group + (0 if linear else ND * (-(-MD // group) * group))
     extra = (4 * NF + 3 * NF * t + t + 1 + 1) if gate else 0
     stage = 40 + 64 if K == 34 else 0
     ggrad = ((0 if gate else 4 * NF) + 3 * NF * t + 12 * t) if grad else 0
@@ -316,13 +324,14 @@ def main():
         gate = net is not None
         fused = solver.fused
         grad_mode = (2 if args.gradients == "least_squares" else 1) if fused else 0
-        rbc = ((1 - frac) * recon_bytes_per_cell(lm, prec, gate=gate, grad=fused)
-               + frac * recon_bytes_per_cell(lm, prec, linear=True, gate=gate, grad=fused))
+        rbc, model = (((1 - frac) * recon_bytes_per_cell(lm, prec, gate=gate, grad=fused, read=r)
+                       + frac * recon_bytes_per_cell(lm, prec, linear=True, gate=gate, grad=fused, read=r))
+                      for r in (True, False))
         variants[name] = {"value": rate, "ms_per_step": ms / args.steps, "wall_s": wall,
                           ("ms_per_step_eager" if args.graph else "ms_per_step_graph"): other_ms / args.steps,
                           "ms_per_step_runs": [r[0] / args.steps for r in per_run],
                           "recon_ms": rms, "recon_bytes_per_cell": rbc, "recon_GBs": rbc * nc / (rms / 1e3) / 1e9,
-                          "fused_gradients": fused, "grad_mode": grad_mode,
+                          "scheme_bytes_per_cell": model, "fused_gradients": fused, "grad_mode": grad_mode,
                           "step_bytes_per_cell_stage": step_bytes_per_cell(lm, prec, recon=rbc, fused=fused),
                           "path_GBs": step_bytes_per_cell(lm, prec, recon=rbc, fused=fused) * rate / 1e9}
         if net is not None:
@@ -398,11 +407,12 @@ def main_tet_p3(args, n=48):
         solver.check()
         rate = nc * 3 * args.steps / (ms / 1e3)
         rms, _ = time_recon_replay(solver, U0, args.steps, args.warmup, torch)
-        rbc = recon_bytes_per_cell(lm, prec)
+        rbc = recon_bytes_per_cell(lm, prec, read=True)
         variants[name] = {"value": rate, "ms_per_step": ms / args.steps, "wall_s": wall, "recon_ms": rms,
                           "recon_bytes_per_cell": rbc, "recon_GBs": rbc * nc / (rms / 1e3) / 1e9,
-                          "step_bytes_per_cell_stage": step_bytes_per_cell(lm, prec, viscous=False),
-                          "path_GBs": step_bytes_per_cell(lm, prec, viscous=False) * rate / 1e9}
+                          "scheme_bytes_per_cell": recon_bytes_per_cell(lm, prec),
+                          "step_bytes_per_cell_stage": step_bytes_per_cell(lm, prec, viscous=False, recon=rbc),
+                          "path_GBs": step_bytes_per_cell(lm, prec, viscous=False, recon=rbc) * rate / 1e9}
         print(f"[bench] {name}: {rate:.3e} cell-stage/s, {ms / args.steps:.3f} ms/step, recon {rms:.3f} ms",
               file=sys.stderr, flush=True)
         del solver
@@ -455,12 +465,13 @@ def main_hex_p4(args, n=64):
         solver.check()
         rate = nc * 3 * args.steps / (ms / 1e3)
         rms, _ = time_recon_replay(solver, U0, args.steps, args.warmup, torch)
-        rbc = recon_bytes_per_cell(lm, prec)
+        rbc = recon_bytes_per_cell(lm, prec, read=True)
         variants[name] = {"value": rate, "ms_per_step": ms / args.steps, "wall_s": wall, "recon_ms": rms,
                           "recon_bytes_per_cell": rbc, "recon_GBs": rbc * nc / (rms / 1e3) / 1e9,
+                          "scheme_bytes_per_cell": recon_bytes_per_cell(lm, prec),
                           "arena_GB": lm.arena_bytes(prec) / 1e9,
-                          "step_bytes_per_cell_stage": step_bytes_per_cell(lm, prec, viscous=False),
-                          "path_GBs": step_bytes_per_cell(lm, prec, viscous=False) * rate / 1e9}
+                          "step_bytes_per_cell_stage": step_bytes_per_cell(lm, prec, viscous=False, recon=rbc),
+                          "path_GBs": step_bytes_per_cell(lm, prec, viscous=False, recon=rbc) * rate / 1e9}
         print(f"[bench] {name}: {rate:.3e} cell-stage/s, {ms / args.steps:.3f} ms/step, recon {rms:.3f} ms "
               f"({variants[name]['recon_GBs']:.0f} GB/s algorithmic)", file=sys.stderr, flush=True)
         del solver
