@@ -1108,8 +1108,8 @@ bool nt_streams(const ReconArgs<T>& A, int K) {
 // 421 us).  Streams that fit the Infinity Cache gain nothing from a shared CU
 // cache either, whatever the wave count (even FP32 P2 tetrahedra, one wave / four:
 // 2,058 waves 84 / 98 us, 2,287 103 / 122, 2,532 124 / 137).  Four waves share a
-// CU's cache when the call is large and even (64^3 FP64 302 against 307 us,
-// 196,608 P3 FP64 tets 397 against 411 us).
+// CU's cache when the call is large and even (64^3 FP64 281 against 287 us, FP32
+// 186 against 201, 196,608 P3 FP64 tets 393 against 409 us).
 inline int recon_block_waves(int64_t waves, bool uneven, bool nt) { return !nt || waves <= 2048 || uneven ? 1 : 4; }
 
 template <class T, int K, bool GATE, int GRAD>
